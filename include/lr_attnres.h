@@ -446,16 +446,19 @@ int lr_attnres_route_gather_bwd(const void *V, const void *K, int64_t source, co
  *   neff [T][N] fp32, overwritten, or NULL: exp(-sum_i alpha_i log alpha_i)
  *        of site j's weights for token n.
  * With projected or sliced keys, S, T and r at most 64 and d a multiple of
- * 8, one fused launch reads the stack once for all sites; otherwise (full-rank
- * keys, larger S, T or r, other d) the library runs the sites one after the
- * other, each as lr_attnres_route_fwd over its prefix (and
- * lr_attnres_route_neff), so every site's H row is bit for bit that call's.
+ * 8, one fused launch reads the stack once for all sites; so does a second
+ * form for sliced keys of any r > 64 (bf16 storage, S and T at most 64, d and
+ * r multiples of 8, Q 16-byte aligned).  Otherwise (full-rank keys, larger S
+ * or T, wide projected keys, wide keys in fp32, other d or r) the library runs
+ * the sites one after the other, each as lr_attnres_route_fwd over its prefix
+ * (and lr_attnres_route_neff), so every site's H row is bit for bit that
+ * call's.
  * EINVAL: first < 1, T < 1, first + T - 1 > S, or the conditions of
  * lr_attnres_route_fwd (V, H 16-byte aligned; K, Q, neff element aligned; no
  * output may overlap an input or the other output).  EUNSUPPORTED: N above
  * 2^30, or, site by site, what lr_attnres_route_fwd refuses for the last site
- * (first + T - 1 sources).  In the fused launch non-finite source values are
- * not confined to the sites that read them: a source past a site's prefix
+ * (first + T - 1 sources).  In the fused launch for r <= 64 non-finite source
+ * values are not confined to the sites that read them: a source past a site's prefix
  * enters that site's product with weight 0, and 0 * inf is NaN.
  */
 int lr_attnres_route_all_fwd(const void *V, const void *K, const float *Q, void *H, float *neff,
@@ -474,12 +477,15 @@ int lr_attnres_route_all_fwd(const void *V, const void *K, const float *Q, void 
  *   dK [S][N][r] storage `dtype`: dL/dK with projected keys, else NULL;
  *   dQ [T][r] fp32: row j is dL/dQ[j], summed over the N tokens;
  *   workspace: lr_attnres_route_all_bwd_workspace_bytes(...) bytes of device
- *        memory, 4-byte aligned (per-workgroup dQ partials).
+ *        memory, 4-byte aligned (per-workgroup dQ partials; for sliced keys of
+ *        r > 64 also 256 bytes per token and site).
  * accumulate = 0 overwrites dV, dK and dQ; 1 adds the gradients to them.
  * Where the fused forward applies and storage is bf16, one fused launch moves
  * each source row, upstream row and dV row once for all sites and rounds each
- * gradient to bf16 once.  Otherwise (full-rank keys, fp32 storage, larger S,
- * T or r, other d) the sites run one after the other as accumulating
+ * gradient to bf16 once; sliced keys of r > 64 that the forward fuses take
+ * three launches and likewise round each gradient once.  Otherwise (full-rank
+ * keys, fp32 storage, larger S or T, wide projected keys, other d or r) the
+ * sites run one after the other as accumulating
  * lr_attnres_route_bwd calls over their prefixes, after a fill kernel has
  * zeroed dV, dK and dQ when overwriting (no memset); a source's gradient is
  * then rounded to the storage after each site that reads it, and dQ row j is

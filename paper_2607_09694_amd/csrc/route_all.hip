@@ -65,6 +65,51 @@ __device__ __forceinline__ void load_group(const uint16_t *__restrict__ vrow, si
     }
 }
 
+// Scores and weights of one token's sites from keys wider than kAllMaxRank,
+// into LDS as all_site_weights leaves them.
+template <int MT>
+__device__ __forceinline__ void wide_site_weights(const AllArgs &a, int64_t n, float *alpha)
+{
+    __shared__ float rho[kAllMaxSources];
+    const int lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
+    const int col = lane & 15, ks = lane >> 4;
+    f32x4_t D[4], G[4];
+    float rho_l[4], s[4][4], al[4][4];
+    wide_products<MT, false>(a, n, nullptr, a.S, reinterpret_cast<unsigned char *>(alpha), rho, D,
+                             G, rho_l);
+    site_softmax<true>(a, n, wave, col, ks, D, rho_l, s, al);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+            alpha[(16 * wave + 4 * ks + e) * kAlphaRow + 16 * nt + col] = al[nt][e];
+    lds_barrier();
+}
+
+// One slab of h for every site, each over the sources of its prefix only, on
+// the vector units (see all_fwd_token).  Lanes as there: 8 columns, every
+// fourth site.
+__device__ __forceinline__ void mix_prefixes(const AllArgs &a, const float *alpha, const uint16_t *V,
+                                          uint16_t *H, size_t plane, int ks, bool ok)
+{
+    if (!ok)
+        return;
+#pragma unroll 1
+    for (int site = ks; site < a.T; site += 4) {
+        float acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+        for (int i = 0; i < a.first + site; ++i) {
+            const float w = alpha[site * kAlphaRow + i];
+            float x[8];
+            widen(load_raw<uint16_t, 8>(V + i * plane), x);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                acc[e] = fmaf(w, x[e], acc[e]);
+        }
+        store_raw<uint16_t, 8>(H + site * plane, Narrow<uint16_t, 8>::run(acc));
+    }
+}
+
 // bf16 storage: 32 sources per MFMA step, at most 2 steps (S <= 64).  One
 // source group is in flight while the previous one is multiplied; the first
 // is issued before the weights are computed.  Every site tile multiplies
@@ -73,6 +118,7 @@ __device__ __forceinline__ void load_group(const uint16_t *__restrict__ vrow, si
 // matrix cores save.  One token: with PERSIST, its keys come in kown and
 // the next token's keys (token nnext) are loaded into kown once its
 // weights are formed, so that they arrive during its mix.
+// RP = 0: keys wider than kAllMaxRank, scored by wide_products.
 template <int MT, int RP, bool PERSIST>
 __device__ __forceinline__ void all_fwd_token(const AllArgs &a, int64_t n, float *alpha,
                                               u32x4_t *kown, int64_t nnext)
@@ -93,6 +139,8 @@ __device__ __forceinline__ void all_fwd_token(const AllArgs &a, int64_t n, float
         all_site_weights<uint16_t, RP>(a, n, alpha, nullptr, nullptr, kown);
         if (nnext < a.N)
             load_site_keys<RP>(a, nnext, kown);
+    } else if constexpr (RP == 0) {
+        wide_site_weights<MT>(a, n, alpha);
     } else {
         all_site_weights<uint16_t, RP>(a, n, alpha);
     }
@@ -155,6 +203,23 @@ __device__ __forceinline__ void all_fwd_token(const AllArgs &a, int64_t n, float
                 }
             }
         }
+        if constexpr (RP == 0) {
+            // A source past a site's prefix enters its product as 0 * value:
+            // an infinite or NaN value would reach sites that don't read it.
+            // Such a slab is mixed again over each site's prefix alone.
+            float bad = 0.0f;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int p = 0; p < 8; ++p)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        bad = fmaf(acc[mt][p][e], 0.0f, bad);
+            if (__any(bad != 0.0f)) {
+                mix_prefixes(a, alpha, V + slab * kAllSlab, H + slab * kAllSlab, plane, ks, ok);
+                continue;
+            }
+        }
         // Lane l holds sites 16 mt + 4 (l / 16) + e, columns c0 .. c0 + 7.
         if (ok) {
             uint16_t *h0 = H + (size_t)(unsigned)(4 * ks) * plane + slab * kAllSlab;
@@ -193,6 +258,16 @@ __global__ __launch_bounds__(kBlock, MT <= 3 ? 2 : 1) void route_all_fwd_bf16(Al
         for (int64_t n = blockIdx.x; n < a.N; n += gridDim.x)
             all_fwd_token<MT, RP, true>(a, n, alpha, kown, n + gridDim.x);
     }
+}
+
+// Keys wider than kAllMaxRank columns: one token per workgroup.
+template <int MT>
+__global__ __launch_bounds__(kBlock, MT <= 3 ? 2 : 1) void route_all_fwd_wide(AllArgs a)
+{
+    // The exchange of the products, then the weights.
+    __shared__ __align__(16)
+        float alpha[std::max<int>(wide_exchange_bytes<MT>() / 4, kAllMaxSources * kAlphaRow)];
+    all_fwd_token<MT, 0, false>(a, blockIdx.x, alpha, nullptr, 0);
 }
 
 // fp32 storage: 4 sources per MFMA step.
@@ -316,6 +391,19 @@ __global__ __launch_bounds__(kBlock) void route_neff(const T *__restrict__ keys,
 
 }  // namespace
 
+// Wide keys: one pass over the stack for all sites instead of one per site,
+// whatever the number of tokens, sites or sources (49 sources, 48 sites,
+// d = 1024, r = 256: forward 2.1 ms -> 0.11 ms at 2048 tokens; the backward's
+// figures are with its kernels).  r % 8: key rows of whole 16-byte vectors.
+bool all_wide(const AllProblem &p)
+{
+    const int64_t koff = p.d - p.r;
+    return p.dtype == LRAR_DTYPE_BF16 && p.mode == LRAR_MODE_SLICED && p.r > kAllMaxRank &&
+           p.S <= kAllMaxSources &&
+           p.T <= kAllMaxSources && p.d % 8 == 0 && koff % 8 == 0 &&
+           reinterpret_cast<uintptr_t>(p.Q) % 16 == 0;
+}
+
 bool all_fused(const AllProblem &p)
 {
     return (p.mode == LRAR_MODE_PROJECTED || p.mode == LRAR_MODE_SLICED) &&
@@ -336,9 +424,9 @@ int check_all_supported(const AllProblem &p, std::string *why)
     }
     if (all_fused(p))
         return LRAR_OK;
-    // Full-rank keys, or more than 64 sources, sites or key columns: site by
-    // site, each site as the single-site forward over its prefix.  The last
-    // site reads the most sources and binds.
+    // Full-rank keys, wide keys, or more than 64 sources or sites (the wide
+    // launch takes no more than the sites do): site by site, each site as the single-site forward over its prefix.
+    // The last site reads the most sources and binds.
     std::string w;
     if (check_supported(all_site_problem(p, p.T - 1), false, &w) != LRAR_OK) {
         *why = "all-sites routing, site by site: " + w;
@@ -351,6 +439,17 @@ int launch_all_fwd(const AllProblem &p, hipStream_t st, std::string *err)
 {
     if (p.N == 0)
         return LRAR_OK;
+    if (all_wide(p)) {
+        const AllArgs a = all_wide_args(p);
+        const dim3 grid((unsigned)p.N), block(kBlock);
+        switch ((a.T + 15) / 16) {
+        case 1: hipLaunchKernelGGL(route_all_fwd_wide<1>, grid, block, 0, st, a); break;
+        case 2: hipLaunchKernelGGL(route_all_fwd_wide<2>, grid, block, 0, st, a); break;
+        case 3: hipLaunchKernelGGL(route_all_fwd_wide<3>, grid, block, 0, st, a); break;
+        default: hipLaunchKernelGGL(route_all_fwd_wide<4>, grid, block, 0, st, a); break;
+        }
+        return hip_status(hipGetLastError(), "route_all_fwd_wide", err);
+    }
     if (!all_fused(p)) {
         // One launch of the single-site forward (and N_eff) per site.
         const size_t es = p.dtype == LRAR_DTYPE_BF16 ? 2 : 4;

@@ -631,8 +631,13 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st)
 
 size_t all_bwd_workspace_bytes(const AllProblem &p)
 {
-    if (!all_bwd_fused(p))
-        return bwd_workspace_bytes(all_site_problem(p, p.T - 1));
+    if (!all_bwd_fused(p)) {
+        // 0 where the call is refused or has no tokens.  Wide keys may still
+        // run site by site (an unaligned Q).
+        const size_t site = bwd_workspace_bytes(all_site_problem(p, p.T - 1));
+        return site > 0 && all_wide(p) ? std::max(site, wide_bwd_workspace_bytes(p.N, p.T, p.r))
+                                       : site;
+    }
     return (size_t)all_bwd_workgroups(p.N) * (size_t)p.T * (size_t)p.r * sizeof(float);
 }
 
@@ -644,8 +649,8 @@ int check_all_bwd_supported(const AllProblem &p, std::string *why)
     }
     if (all_bwd_fused(p))
         return LRAR_OK;
-    // Full-rank keys, fp32 storage, or more than 64 sources, sites or key
-    // columns: site by site, each site's accumulating single-site backward.
+    // Full-rank keys, fp32 storage, wide keys, or more than 64 sources or
+    // sites (the wide launch takes no more than the sites do): site by site, each site's accumulating single-site backward.
     std::string w;
     if (check_supported(all_site_problem(p, p.T - 1), true, &w) != LRAR_OK) {
         *why = "all-sites backward, site by site: " + w;
@@ -657,6 +662,8 @@ int check_all_bwd_supported(const AllProblem &p, std::string *why)
 int launch_all_bwd(const AllProblem &p, const void *dH, void *dV, void *dK, float *dQ, void *ws,
                    bool accumulate, hipStream_t st, std::string *err)
 {
+    if (all_wide(p))
+        return launch_wide_bwd(p, dH, dV, dQ, ws, accumulate, st, err);
     if (!all_bwd_fused(p)) {
         // Site by site: each site's backward adds into the gradients of its
         // prefix and into its row of dQ, after one zero fill when overwriting.

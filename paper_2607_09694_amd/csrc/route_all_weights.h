@@ -5,6 +5,8 @@
 
 #include "route_common.h"
 
+#include <algorithm>
+
 namespace lrar {
 
 constexpr int kAllMaxSources = 64;  // sources S, and sites T
@@ -58,6 +60,86 @@ struct AllArgs {
 // all 16: four DPP moves (group_sum / group_max over groups of 16).
 __device__ __forceinline__ float row16_sum(float x) { return group_sum(x, 16); }
 __device__ __forceinline__ float row16_max(float x) { return group_max(x, 16); }
+
+// Whether site `site` reads source i.
+__device__ __forceinline__ bool read_by(const AllArgs &a, int site, int i)
+{
+    return site < a.T && i < a.first + site;
+}
+
+// Softmax over depth of the 16 sites of tile `wave`, from the score products
+// D[nt][e] = rho_i Q_j . kbar_i: lane l holds sites j = 16 wave + 4 (l / 16) + e
+// against sources i = 16 nt + (l mod 16), irho[nt] = 1 / rho_i.  Leaves the
+// scores (-inf past a site's prefix) and the weights (0 there and for absent
+// sites), and writes N_eff if asked for.  STRICT: a NaN or infinite score of
+// a source that the site reads makes the site's weights NaN, as in the
+// single-site kernels; otherwise such a source drops out.
+template <bool STRICT>
+__device__ __forceinline__ void site_softmax(const AllArgs &a, int64_t n, int wave, int col,
+                                             int ks, const f32x4_t (&D)[4],
+                                             const float (&irho)[4], float (&s)[4][4],
+                                             float (&al)[4][4])
+{
+    // No contraction: the same operations, hence the same bits, in every
+    // kernel that calls it.
+#pragma clang fp contract(off)
+    float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        const int i = 16 * nt + col;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int site = 16 * wave + 4 * ks + e;
+            // STRICT: irho holds rho itself (one rounding less than with its
+            // reciprocal).
+            s[nt][e] = !read_by(a, site, i) ? -INFINITY
+                       : STRICT             ? D[nt][e] / irho[nt]
+                                            : D[nt][e] * irho[nt];
+            m[e] = fmaxf(m[e], s[nt][e]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        m[e] = row16_max(m[e]);
+    float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool in = STRICT ? read_by(a, 16 * wave + 4 * ks + e, 16 * nt + col)
+                                   : s[nt][e] > -INFINITY;
+            al[nt][e] = in ? expf(s[nt][e] - m[e]) : 0.0f;
+            z[e] += al[nt][e];
+        }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        z[e] = row16_sum(z[e]);
+    float sa[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float inv = (STRICT ? z[e] != 0.0f : z[e] > 0.0f) ? 1.0f / z[e] : 0.0f;
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const bool some = STRICT ? al[nt][e] != 0.0f : al[nt][e] > 0.0f;
+            const float ex = al[nt][e];
+            al[nt][e] *= inv;
+            if (some)
+                sa[e] = fmaf(STRICT ? ex : al[nt][e], s[nt][e] - m[e], sa[e]);
+        }
+    }
+    if (a.neff) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sa[e] = row16_sum(sa[e]);
+            const int site = 16 * wave + 4 * ks + e;
+            // STRICT: z exp(-t / z) with the sums of the exponentials, as
+            // route_neff forms it (half the error of the other form).
+            if (col == 0 && site < a.T)
+                a.neff[(size_t)site * a.N + n] =
+                    STRICT ? z[e] * expf(-sa[e] / z[e]) : expf(logf(z[e]) - sa[e]);
+        }
+    }
+}
 
 template <int RP>
 __device__ __forceinline__ void load_site_keys(const AllArgs &a, int64_t n, u32x4_t *kraw)
@@ -196,11 +278,8 @@ __device__ __forceinline__ void all_site_weights(const AllArgs &a, int64_t n, fl
         }
     }
 
-    // Scores: lane l holds sites 16 w + 4 (l / 16) + e against sources
-    // 16 nt + (l mod 16).
     // One reciprocal per key instead of a division per score.
-    float s[4][4];
-    float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    float irho[4];
     const float inv_r = 1.0f / (float)a.r;
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
@@ -208,55 +287,295 @@ __device__ __forceinline__ void all_site_weights(const AllArgs &a, int64_t n, fl
         t += __shfl_xor(t, 16, kWaveSize);
         t += __shfl_xor(t, 32, kWaveSize);
         const float rho = sqrtf(fmaf(t, inv_r, a.eps));
-        const float irho = 1.0f / rho;
-        const int i = 16 * nt + col;
+        irho[nt] = 1.0f / rho;
         if (SAVE && wave == 0 && ks == 0)
-            rho_out[i] = rho;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int site = 16 * wave + 4 * ks + e;
-            const bool v = site < a.T && i < a.first + site;
-            s[nt][e] = v ? D[nt][e] * irho : -INFINITY;
-            m[e] = fmaxf(m[e], s[nt][e]);
-        }
+            rho_out[16 * nt + col] = rho;
     }
+    float s[4][4], al[4][4];
+    site_softmax<false>(a, n, wave, col, ks, D, irho, s, al);
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        m[e] = row16_max(m[e]);
-    float ex[4][4], z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+            alpha[(16 * wave + 4 * ks + e) * kAlphaRow + 16 * nt + col] = al[nt][e];
+    lds_barrier();
+}
+
+// ---------------------------------------------------------------------------
+// Sliced keys wider than kAllMaxRank columns, bf16 storage.
+// ---------------------------------------------------------------------------
+
+// 8 fp32 values as three bf16 operands whose sum is exact to fp32's 24 bits
+// (hi = RNE(v), mid = RNE(v - hi), lo = RNE(v - hi - mid)): products with
+// bf16 values then lose nothing that fp32 would keep.
+__device__ __forceinline__ void split3(const float (&v)[8], bf16x8_t &hi, bf16x8_t &mid,
+                                       bf16x8_t &lo)
+{
+    u32x4_t h, m, l;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const unsigned hw = pack_bf16x2(v[2 * k], v[2 * k + 1]);
+        const float r0 = v[2 * k] - bf16_lo(hw), r1 = v[2 * k + 1] - bf16_hi(hw);
+        const unsigned mw = pack_bf16x2(r0, r1);
+        h[k] = hw;
+        m[k] = mw;
+        l[k] = pack_bf16x2(r0 - bf16_lo(mw), r1 - bf16_hi(mw));
+    }
+    hi = __builtin_bit_cast(bf16x8_t, h);
+    mid = __builtin_bit_cast(bf16x8_t, m);
+    lo = __builtin_bit_cast(bf16x8_t, l);
+}
+
+// Arguments of the wide-key kernels.  Sources past the last site's prefix are
+// left out: no site reads them.
+inline AllArgs all_wide_args(const AllProblem &p)
+{
+    AllArgs a;
+    a.V = a.keys = p.V;
+    a.Q = p.Q;
+    a.H = p.H;
+    a.neff = p.neff;
+    a.S = (int)std::min<int64_t>(p.S, p.first + p.T - 1);
+    a.d = a.krow = (int)p.d;
+    a.r = (int)p.r;
+    a.koff = (int)(p.d - p.r);
+    a.first = (int)p.first;
+    a.T = (int)p.T;
+    a.N = p.N;
+    a.eps = p.eps;
+    a.kvec = true;
+    return a;
+}
+
+// LDS exchange of wide_products, in bytes: one accumulator set per wave.
+template <int MT> constexpr int wide_exchange_bytes() { return kWaves * MT * 4 * kWaveSize * 16; }
+
+// The products of one token that contract whole rows: D = Q [16 MT x r] * K^T
+// [r x 64] (Q as three bf16 terms), and with GRAD also G = dH [16 MT x d] *
+// V^T [d x 64].  On return wave w holds tile w's rows: D[nt], G[nt] of sites
+// 16 w + 4 (l / 16) + e against source 16 nt + (l mod 16); rho_l[nt] = rho of
+// those sources, and rho (LDS, 64 floats) of all.
+// Without GRAD the columns are those of the key; with it those of the whole
+// row, first the ones before the key, then the key's.  The waves share the
+// columns, 64 at a time in turn, so that each line of the token's rows is
+// read once: with a tile of sites per wave, and so every row read by all four,
+// the rows came from beyond the L2 each time (the planes of a stack lie a
+// power of two apart and share the L2's sets) and the backward took 333 us
+// instead of 256 (49 sources, 48 sites, d = 1024, r = 256, 2048 tokens).  The waves'
+// partial sums meet in LDS and are added in wave order.  Steps of 32 columns,
+// AHEAD of them in flight.  No load sits behind a branch, so that the
+// compiler's wait counts leave the later steps in flight: rows past the
+// sources or sites re-read the last one, which reaches only entries that are
+// masked later, and columns past a range's end re-read its last ones against
+// zeros in the other operand.  nsrc: sources that some site reads.
+template <int MT, bool GRAD>
+__device__ __forceinline__ void wide_products(const AllArgs &a, int64_t n, const uint16_t *dH,
+                                              int nsrc, unsigned char *exchange, float *rho,
+                                              f32x4_t (&D)[4], f32x4_t (&G)[4], float (&rho_l)[4])
+{
+#pragma clang fp contract(off)
+    // Steps of source rows in flight, and of the sites' rows (which take MT
+    // times the registers: one step, refilled as soon as it has been used,
+    // where two waves per SIMD leave no room for more).
+    constexpr int AHEAD = MT == 1 ? 4 : 2, HA = MT <= 2 ? AHEAD : 1;
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const int lc = lane & 15, ks = lane >> 4;
+    const int key0 = GRAD ? a.koff : 0;  // the key's first column, from `base` on
+    const uint16_t *base = static_cast<const uint16_t *>(a.keys) + n * a.krow + (GRAD ? 0 : a.koff);
+    const size_t plane = (size_t)a.N * a.krow;
+    const uint16_t *rows[4], *hrow[MT];
+    const float *qrow[MT];
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
+        rows[nt] = base + (size_t)min(16 * nt + lc, nsrc - 1) * plane;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            ex[nt][e] = s[nt][e] > -INFINITY ? expf(s[nt][e] - m[e]) : 0.0f;
-            z[e] += ex[nt][e];
+    for (int mt = 0; mt < MT; ++mt) {
+        const int site = min(16 * mt + lc, a.T - 1);
+        qrow[mt] = a.Q + (size_t)site * a.r - key0;
+        hrow[mt] = GRAD ? dH + ((size_t)site * a.N + n) * a.d : nullptr;
+    }
+    f32x4_t pd[MT][4], pg[MT][4];
+    float ss[4];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        ss[nt] = 0.0f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            pd[mt][nt] = pg[mt][nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    // Columns [beg, end), KEY: of the key.
+    auto range = [&](auto keyc, int beg, int end) {
+        constexpr bool KEY = decltype(keyc)::value;
+        u32x4_t v[AHEAD][4], h[HA][MT];
+        f32x4_t q[HA][MT][2];
+        // Column of the wave's step s (this lane's 8).
+        auto column = [&](int s) { return beg + 64 * (wave + kWaves * (s >> 1)) + 32 * (s & 1) + 8 * ks; };
+        auto load_v = [&](int s, int u) {
+            const int c = min(column(s), end - 8);
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                v[u][nt] = load_raw<uint16_t, 8>(rows[nt] + c);
+        };
+        auto load_h = [&](int s, int u, int mt) {
+            if (GRAD)
+                h[u][mt] = load_raw<uint16_t, 8>(hrow[mt] + min(column(s), end - 8));
+        };
+        auto load_q = [&](int s, int u, int mt) {
+            if (KEY) {
+                const float *p = qrow[mt] + min(column(s), end - 8);
+                q[u][mt][0] = *reinterpret_cast<const f32x4_t *>(p);
+                q[u][mt][1] = *reinterpret_cast<const f32x4_t *>(p + 4);
+            }
+        };
+        auto use = [&](int s, int u) {
+            const bool ok = column(s) < end;
+            if (GRAD) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const bf16x8_t A =
+                        __builtin_bit_cast(bf16x8_t, ok ? h[u % HA][mt] : u32x4_t{0u, 0u, 0u, 0u});
+                    load_h(s + HA, u % HA, mt);
+#pragma unroll
+                    for (int nt = 0; nt < 4; ++nt)
+                        pg[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            A, __builtin_bit_cast(bf16x8_t, v[u][nt]), pg[mt][nt], 0, 0, 0);
+                }
+            }
+            if (KEY) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    float x[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        x[e] = ok ? q[u % HA][mt][e / 4][e % 4] : 0.0f;
+                    bf16x8_t A[3];
+                    split3(x, A[2], A[1], A[0]);
+                    load_q(s + HA, u % HA, mt);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+#pragma unroll
+                        for (int nt = 0; nt < 4; ++nt)
+                            pd[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                A[k], __builtin_bit_cast(bf16x8_t, v[u][nt]), pd[mt][nt], 0, 0, 0);
+                }
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt) {
+                    float y[8], t = 0.0f;
+                    widen(v[u][nt], y);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        t = fmaf(y[e], y[e], t);
+                    ss[nt] += ok ? t : 0.0f;
+                }
+            }
+        };
+        const int units = (end - beg + 63) / 64;
+        const int steps = 2 * ((units - wave + kWaves - 1) / kWaves);
+        if (steps <= 0)
+            return;
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (u < HA)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    load_h(u, u, mt);
+                    load_q(u, u, mt);
+                }
+            load_v(u, u);
         }
+        for (int s = 0; s < steps; s += AHEAD)
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        z[e] = row16_sum(z[e]);
-    float sa[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int u = 0; u < AHEAD; ++u) {
+                __builtin_amdgcn_sched_barrier(0);
+                use(s + u, u);
+                __builtin_amdgcn_sched_barrier(0);
+                load_v(s + u + AHEAD, u);
+            }
+    };
+    if (key0 > 0)
+        range(std::false_type{}, 0, key0);
+    range(std::true_type{}, key0, key0 + a.r);
+
+    // The waves' shares, added in wave order: sum k^2, then D, then G.
+    f32x4_t *ex = reinterpret_cast<f32x4_t *>(exchange);
+    float *exs = reinterpret_cast<float *>(exchange);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        ss[nt] += __shfl_xor(ss[nt], 16, kWaveSize);
+        ss[nt] += __shfl_xor(ss[nt], 32, kWaveSize);
+        if (ks == 0)
+            exs[wave * kAllMaxSources + 16 * nt + lc] = ss[nt];
+    }
+    lds_barrier();
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+            t += exs[w * kAllMaxSources + 16 * nt + lc];
+        rho_l[nt] = sqrtf(t / (float)a.r + a.eps);
+        if (wave == 0 && ks == 0)
+            rho[16 * nt + lc] = rho_l[nt];
+    }
+    lds_barrier();
+    auto meet = [&](const f32x4_t (&part)[MT][4], f32x4_t (&sum)[4]) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                ex[((wave * MT + mt) * 4 + nt) * kWaveSize + lane] = part[mt][nt];
+        lds_barrier();
+        const int tile = min(wave, MT - 1);  // waves past the tiles: masked later
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            sum[nt] = ex[(tile * 4 + nt) * kWaveSize + lane];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w)
+                sum[nt] += ex[((w * MT + tile) * 4 + nt) * kWaveSize + lane];
+        }
+        lds_barrier();
+    };
+    meet(pd, D);
+    if (GRAD)
+        meet(pg, G);
+}
+
+// The softmax gradient of the 16 sites of tile `wave` from the value dots
+// G[nt][e] = dH_j . o_i, in the layout of site_softmax:
+//     ds = alpha (G - sum alpha G),  cq = ds / rho,
+// and skk[nt] = sum over the lane's 4 sites of ds s (the RMSNorm term of the
+// sources' key gradients).  Entries past a site's prefix are 0.
+__device__ __forceinline__ void wide_softmax_grad(const AllArgs &a, int wave, int col, int ks,
+                                                  const f32x4_t (&G)[4], const float (&rho_l)[4],
+                                                  const float (&s)[4][4],
+                                                  const float (&al)[4][4], float (&cq)[4][4],
+                                                  float (&skk)[4])
+{
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+        skk[nt] = 0.0f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int site = 16 * wave + 4 * ks + e;
-        const float inv = z[e] > 0.0f ? 1.0f / z[e] : 0.0f;
+        float gb = 0.0f;
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+            if (read_by(a, site, 16 * nt + col))
+                gb = fmaf(al[nt][e], G[nt][e], gb);
+        gb = row16_sum(gb);
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
-            const float al = ex[nt][e] * inv;
-            if (ex[nt][e] > 0.0f)
-                sa[e] = fmaf(al, s[nt][e] - m[e], sa[e]);
-            alpha[site * kAlphaRow + 16 * nt + col] = al;
+            cq[nt][e] = 0.0f;
+            if (read_by(a, site, 16 * nt + col)) {
+                const float ds = al[nt][e] * (G[nt][e] - gb);
+                cq[nt][e] = ds / rho_l[nt];
+                skk[nt] = fmaf(ds, s[nt][e], skk[nt]);
+            }
         }
     }
-    if (a.neff) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sa[e] = row16_sum(sa[e]);
-            const int site = 16 * wave + 4 * ks + e;
-            if (col == 0 && site < a.T)
-                a.neff[(size_t)site * a.N + n] = expf(logf(z[e]) - sa[e]);
-        }
-    }
-    lds_barrier();
 }
 
 // Pairs of bf16 from two packed words: the low halves (lo_pair) or the

@@ -164,6 +164,13 @@ int check_all_supported(const AllProblem &p, std::string *why);
 // Whether the fused all-sites kernels take the problem (projected or sliced
 // keys, S, T, r <= 64, d % 8 == 0); otherwise the sites run one by one.
 bool all_fused(const AllProblem &p);
+// Whether the fused kernels of wide keys take it (bf16 storage, sliced keys
+// of more than 64 columns, S and T <= 64, 16-byte key rows).
+bool all_wide(const AllProblem &p);
+// Their backward; the workspace is 4-byte aligned, dK does not exist.
+size_t wide_bwd_workspace_bytes(int64_t N, int64_t T, int64_t r);
+int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
+                    bool accumulate, hipStream_t st, std::string *err);
 // The single-site problem of site j of an all-sites problem.
 Problem all_site_problem(const AllProblem &p, int64_t j);
 

@@ -1,0 +1,39 @@
+"""What the all-sites calls accept with sliced keys wider than 64 columns,
+checked on the host: the wide launch takes no problem that the sites refuse
+one by one, and needs no workspace without tokens."""
+import ctypes
+
+import pytest
+
+import paper_2607_09694_amd as lr
+
+BF16, F32 = 1, 0
+
+
+def _workspace(S, N, d, r, first, T, dtype):
+    return lr.load_library().lr_attnres_route_all_bwd_workspace_bytes(S, N, d, r, first, T,
+                                                                      lr.SLICED, dtype)
+
+
+@pytest.mark.parametrize("S,N,d,r,first,T,dtype,wide", [
+    (49, 100, 1024, 256, 2, 48, BF16, True),
+    (64, 100, 1024, 72, 1, 64, BF16, True),
+    (49, 100, 1024, 260, 2, 48, BF16, None),    # r above the backward's 256: refused
+    (49, 100, 1024, 100, 2, 48, BF16, False),   # r % 8 != 0
+    (49, 100, 1024, 256, 2, 48, F32, False),    # fp32 storage
+    (65, 100, 1024, 256, 2, 40, BF16, False),   # S > 64
+    (49, 0, 1024, 256, 2, 48, BF16, None),      # no tokens
+])
+def test_workspace_names_the_route(S, N, d, r, first, T, dtype, wide):
+    need = _workspace(S, N, d, r, first, T, dtype)
+    coefficients = N * T * 64 * 4
+    assert need == 0 if wide is None else (need > coefficients) == wide
+
+
+def test_rank_above_the_backward_limit_stays_refused():
+    lib = lr.load_library()
+    a = [0x10_0000_0000 * k for k in range(1, 7)]
+    rc = lib.lr_attnres_route_all_bwd(a[0], None, a[1], a[2], a[3], None, a[4], a[5], 1 << 34, 49,
+                                      100, 1024, 264, 2, 48, lr.SLICED, BF16,
+                                      ctypes.c_float(1e-6), 0, None)
+    assert rc == 2 and b"site by site" in lib.lr_attnres_last_error()

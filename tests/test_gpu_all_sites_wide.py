@@ -1,0 +1,119 @@
+"""GPU parity of the all-sites calls with sliced keys wider than 64 columns
+(bf16 storage), forward and backward, against the fp64 oracle: one to four
+site tiles and source tiles, keys that end inside a 32-column step or start
+inside one, ragged slabs, sources that no site reads, one token and more
+tokens than dQ shares, accumulation, bitwise reruns, and non-finite values
+confined to the sites that read them.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2607_09694_amd as lr
+from paper_2607_09694_amd.inputs import SLICED, bf16_bits_from_f32, f32_from_bf16_bits, \
+    make_host_problem
+from parity import check_bf16_grown, check_bf16_key_grad, check_bf16_value, check_dq, check_f32
+from test_gpu_all_sites_bwd import _queries, _upstream, dev, to_dev, to_host  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+# (S, T, first, N, d, r)
+CASES = [
+    (9, 8, 2, 13, 256, 72),       # one tile; the key starts inside a 32-column step
+    (33, 32, 2, 5, 200, 128),     # two site tiles, three source tiles, ragged slab
+    (49, 48, 2, 7, 1024, 256),    # the paper's model, r = 256
+    (64, 64, 1, 3, 520, 256),     # every limit
+    (20, 6, 3, 9, 128, 128),      # the whole row; sources 8..19 read by no site
+    (17, 1, 17, 1, 136, 80),      # one site, one token, one source past a tile
+    (5, 4, 2, 1100, 96, 96),      # fewer than 128 columns, several tokens per share
+]
+
+
+def _run(dev, case, seed, accumulate=False):
+    S, T, first, N, d, r = case
+    p = make_host_problem(SLICED, S, N, d, r, dtype="bf16", seed=seed)
+    Q, dH = _queries(T, r, seed + 1), _upstream(T, N, d, seed + 2)
+    V, Qd, dHd = to_dev(p.V, dev), to_dev(Q, dev), to_dev(dH, dev)
+    return p, Q, dH, V, Qd, dHd
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "S{}-T{}-f{}-N{}-d{}-r{}".format(*c))
+@pytest.mark.parametrize("accumulate", [False, True], ids=["write", "add"])
+def test_wide_keys_match_oracle(dev, case, accumulate):  # noqa: F811
+    S, T, first, N, d, r = case
+    p, Q, dH, V, Qd, dHd = _run(dev, case, seed=S + T + N)
+    Q64 = Q.astype(np.float64)
+    rV, _, rQ = oracle.route_all_bwd(p.V, None, Q64, dH, SLICED, first, r=r)
+    out = None
+    if accumulate:
+        rng = np.random.default_rng(5)
+        dV0 = bf16_bits_from_f32(rng.standard_normal((S, N, d)).astype(np.float32))
+        dQ0 = rng.standard_normal((T, r)).astype(np.float32)
+        out = (to_dev(dV0, dev), None, to_dev(dQ0, dev))
+        rV, rQ = rV + f32_from_bf16_bits(dV0), rQ + dQ0
+    dV, dK, dQ = lr.route_all_bwd(V, None, Qd, dHd, SLICED, first, out=out, accumulate=accumulate)
+    H, ne = lr.route_all_fwd(V, None, Qd, SLICED, first)
+    torch.cuda.synchronize()
+    Hr, NEr = oracle.route_all_fwd(p.V, None, Q64, SLICED, first, r=r)
+    check_bf16_value("H", to_host(H), Hr)
+    check_f32("neff", to_host(ne), NEr)
+    assert dK is None
+    gV = to_host(dV)
+    check_bf16_grown("dV", gV[..., :d - r], rV[..., :d - r])
+    check_bf16_key_grad("dV key columns", gV[..., d - r:], rV[..., d - r:])
+    if first > 1 or T > 1:
+        check_dq("dQ", to_host(dQ), rQ)
+    if not accumulate and first + T - 1 < S:
+        assert not bool(dV[first + T - 1:].float().abs().max() > 0)
+
+
+def test_wide_keys_rerun_bitwise_and_unaligned_workspace(dev):  # noqa: F811
+    case = (33, 20, 3, 70, 264, 136)
+    _, _, _, V, Qd, dHd = _run(dev, case, seed=3)
+    a = lr.route_all_bwd(V, None, Qd, dHd, SLICED, case[2])
+    need = lr.route_all_bwd_workspace_bytes(*case[:1], *case[3:], case[2], case[1], SLICED,
+                                            torch.bfloat16)
+    ws = torch.empty((need + 4,), dtype=torch.uint8, device=dev)[4:]
+    out = (torch.full_like(a[0], 7.0), None, torch.full_like(a[2], 7.0))
+    b = lr.route_all_bwd(V, None, Qd, dHd, SLICED, case[2], out=out, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(a[0].view(torch.int16), b[0].view(torch.int16)) and torch.equal(a[2], b[2])
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("column", [0, 250], ids=["value", "key"])
+def test_wide_keys_confine_non_finite_values(dev, value, column):  # noqa: F811
+    """A non-finite value of source 11 at token 2 reaches the sites that read
+    it and no other (their own single-site results stay what they were), and
+    a source that no site reads is not read at all; a non-finite upstream
+    value of the first site reaches only the sources that this site reads."""
+    S, T, first, N, d, r = 14, 12, 2, 5, 256, 128
+    _, _, _, V, Qd, dHd = _run(dev, (S, T, first, N, d, r), seed=9)
+    H0, ne0 = lr.route_all_fwd(V, None, Qd, SLICED, first)
+    dV0, _, dQ0 = lr.route_all_bwd(V, None, Qd, dHd, SLICED, first)
+    Vb = V.clone()
+    Vb[13] = float("nan")  # past every prefix
+    Vb[11, 2, column] = value
+    H, ne = lr.route_all_fwd(Vb, None, Qd, SLICED, first)
+    dV, _, dQ = lr.route_all_bwd(Vb, None, Qd, dHd, SLICED, first)
+    readers = [j for j in range(T) if first + j > 11]
+    others = [j for j in range(T) if first + j <= 11]
+    other_tokens = [0, 1, 3, 4]
+    assert torch.equal(H[:, other_tokens], H0[:, other_tokens])
+    assert torch.allclose(H[others].float(), H0[others].float(), rtol=2.0 ** -7, atol=1e-6)
+    assert torch.equal(ne[others], ne0[others])
+    assert not bool(torch.isfinite(H[readers][:, 2, column].float()).any())
+    if column >= d - r:
+        assert not bool(torch.isfinite(H[readers][:, 2].float()).any())
+    assert torch.equal(dV[:, other_tokens], dV0[:, other_tokens])
+    assert torch.allclose(dQ[others], dQ0[others], rtol=1e-4, atol=1e-4)
+    assert not bool(torch.isfinite(dQ[readers]).any())
+    assert not bool(dV[13].float().abs().max() > 0)
+    dHb = dHd.clone()
+    dHb[0, 2, column] = value
+    dV, _, dQ = lr.route_all_bwd(V, None, Qd, dHb, SLICED, first)
+    torch.cuda.synchronize()
+    assert torch.allclose(dV[first:].float(), dV0[first:].float(), rtol=2.0 ** -7, atol=1e-4)
+    assert not bool(torch.isfinite(dV[:first, 2, column].float()).any())
+    assert torch.allclose(dQ[1:], dQ0[1:], rtol=1e-4, atol=1e-4)
