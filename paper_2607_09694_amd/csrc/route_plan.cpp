@@ -23,6 +23,9 @@ constexpr int64_t kWgSplitLowRank = 2048;
 constexpr int64_t kWgSplitFull = 1024;
 #endif
 
+// Workgroups below which a backward gives its waves fewer tokens (two per CU).
+constexpr int64_t kFewBlocks = 512;
+
 int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
 }  // namespace
@@ -89,6 +92,17 @@ bool make_plan(const Problem &p, bool bwd, Plan *pl, std::string *why)
         pl->lds = p.mode == LRAR_MODE_FULL ? 0 : (size_t)kWaves * pl->s_pad * sizeof(float);
     } else {
         pl->tpw = p.mode == LRAR_MODE_FULL ? 4 : bwd_tokens_per_wave(pl->nch);
+        // Fewer tokens per wave where there are too few workgroups to keep the
+        // memory busy (step of forward and backward: fp32, 17 sources, d = 768,
+        // 1000 tokens 62 -> 44 us; bf16 rows of 1020 columns, 49 sources, 2048
+        // tokens 986 -> 634; full rank, 20 sources, d = 1280, 2000 tokens 333 ->
+        // 127; at twice kFewBlocks level or 1% slower).  The dq partials, one
+        // row a workgroup, stay within what a caller without a workspace has.
+        const int64_t ncols = p.mode == LRAR_MODE_FULL ? p.d : p.r;
+        while (pl->tpw > 1 && p.N < kFewBlocks * kWaves * pl->tpw &&
+               (p.N / (kWaves * (pl->tpw / 2)) + 1) * ncols * (int64_t)sizeof(float) <=
+                   (int64_t)kNoAllocScratchBytes)
+            pl->tpw /= 2;
         const int64_t per_block = (int64_t)kWaves * pl->tpw;
         pl->nblocks = (int)((p.N + per_block - 1) / per_block);
         pl->lds = (size_t)kWaves * 4 * pl->s_pad * sizeof(float);
