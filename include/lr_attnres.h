@@ -447,12 +447,12 @@ int lr_attnres_route_gather_bwd(const void *V, const void *K, int64_t source, co
  *        of site j's weights for token n.
  * With projected or sliced keys, S, T and r at most 64 and d a multiple of
  * 8, one fused launch reads the stack once for all sites; so does a second
- * form for sliced keys of any r > 64 (bf16 storage, S and T at most 64, d and
- * r multiples of 8, Q 16-byte aligned).  Otherwise (full-rank keys, larger S
- * or T, wide projected keys, wide keys in fp32, other d or r) the library runs
- * the sites one after the other, each as lr_attnres_route_fwd over its prefix
- * (and lr_attnres_route_neff), so every site's H row is bit for bit that
- * call's.
+ * form for sliced keys of any r > 64 and, above 1024 tokens, full-rank keys
+ * (bf16 storage, S and T at most 64, d and r multiples of 8, Q 16-byte
+ * aligned).  Otherwise (full-rank keys of up to 1024 tokens, larger S or T,
+ * wide projected keys, wide keys in fp32, other d or r) the library runs the
+ * sites one after the other, each as lr_attnres_route_fwd over its prefix (and
+ * lr_attnres_route_neff), so every site's H row is bit for bit that call's.
  * EINVAL: first < 1, T < 1, first + T - 1 > S, or the conditions of
  * lr_attnres_route_fwd (V, H 16-byte aligned; K, Q, neff element aligned; no
  * output may overlap an input or the other output).  EUNSUPPORTED: N above
@@ -477,15 +477,18 @@ int lr_attnres_route_all_fwd(const void *V, const void *K, const float *Q, void 
  *   dK [S][N][r] storage `dtype`: dL/dK with projected keys, else NULL;
  *   dQ [T][r] fp32: row j is dL/dQ[j], summed over the N tokens;
  *   workspace: lr_attnres_route_all_bwd_workspace_bytes(...) bytes of device
- *        memory, 4-byte aligned (per-workgroup dQ partials; for sliced keys of
- *        r > 64 also 256 bytes per token and site).
+ *        memory, 4-byte aligned (per-workgroup dQ partials; for full-rank keys
+ *        and sliced keys of r > 64 also 256 bytes per token and site).
  * accumulate = 0 overwrites dV, dK and dQ; 1 adds the gradients to them.
  * Where the fused forward applies and storage is bf16, one fused launch moves
  * each source row, upstream row and dV row once for all sites and rounds each
- * gradient to bf16 once; sliced keys of r > 64 that the forward fuses take
- * three launches and likewise round each gradient once.  Otherwise (full-rank
- * keys, fp32 storage, larger S or T, wide projected keys, other d or r) the
- * sites run one after the other as accumulating
+ * gradient to bf16 once; sliced keys of r > 64 and full-rank keys (any number
+ * of tokens; S and T at most 64, d and r multiples of 8, Q 16-byte aligned)
+ * take three launches and likewise round each gradient once; with full-rank
+ * keys of d <= 1024, dQ row j is then bit for bit site j's dq of
+ * lr_attnres_route_bwd.
+ * Otherwise (fp32 storage, larger S or T, wide projected keys, other d or r)
+ * the sites run one after the other as accumulating
  * lr_attnres_route_bwd calls over their prefixes, after a fill kernel has
  * zeroed dV, dK and dQ when overwriting (no memset); a source's gradient is
  * then rounded to the storage after each site that reads it, and dQ row j is

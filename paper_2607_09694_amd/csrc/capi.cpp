@@ -199,7 +199,7 @@ int route_bwd(const void *V, const void *K, const float *q, const void *dH, void
     if (noalloc)
         rc = lrar::launch_bwd_noalloc(p, dH, dV, dK, dq, st, &why);
     else
-        rc = lrar::launch_bwd(p, dH, dV, dK, dq, workspace, accumulate, st, &why);
+        rc = lrar::launch_bwd(p, dH, dV, dK, dq, workspace, need, accumulate, st, &why);
     if (rc)
         return fail(rc, why);
     return LRAR_OK;

@@ -41,6 +41,12 @@ namespace lrar {
 
 namespace {
 
+// Full-rank forwards of up to this many tokens run site by site, so that there
+// every row of H stays bit for bit the single-site call's (which splits a
+// token's sources over a workgroup up to the same count, in an order of sums
+// that the wide form doesn't have); with more, one pass over the stack.
+constexpr int64_t kFullSitesOneByOne = 1024;
+
 constexpr int kAllFwdGrid = 256;  // persistent workgroups above 48 sites (one per CU)
 
 // Largest prefix read by a site of tile mt (sites 16 mt .. 16 mt + 15).
@@ -398,8 +404,8 @@ __global__ __launch_bounds__(kBlock) void route_neff(const T *__restrict__ keys,
 bool all_wide(const AllProblem &p)
 {
     const int64_t koff = p.d - p.r;
-    return p.dtype == LRAR_DTYPE_BF16 && p.mode == LRAR_MODE_SLICED && p.r > kAllMaxRank &&
-           p.S <= kAllMaxSources &&
+    return p.dtype == LRAR_DTYPE_BF16 && p.mode != LRAR_MODE_PROJECTED &&
+           (p.mode == LRAR_MODE_FULL || p.r > kAllMaxRank) && p.S <= kAllMaxSources &&
            p.T <= kAllMaxSources && p.d % 8 == 0 && koff % 8 == 0 &&
            reinterpret_cast<uintptr_t>(p.Q) % 16 == 0;
 }
@@ -439,7 +445,7 @@ int launch_all_fwd(const AllProblem &p, hipStream_t st, std::string *err)
 {
     if (p.N == 0)
         return LRAR_OK;
-    if (all_wide(p)) {
+    if (all_wide(p) && (p.mode != LRAR_MODE_FULL || p.N > kFullSitesOneByOne)) {
         const AllArgs a = all_wide_args(p);
         const dim3 grid((unsigned)p.N), block(kBlock);
         switch ((a.T + 15) / 16) {

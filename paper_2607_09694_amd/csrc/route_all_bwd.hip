@@ -633,10 +633,12 @@ size_t all_bwd_workspace_bytes(const AllProblem &p)
 {
     if (!all_bwd_fused(p)) {
         // 0 where the call is refused or has no tokens.  Wide keys may still
-        // run site by site (an unaligned Q).
+        // run site by site (an unaligned Q); the last site's workspace covers
+        // all full-rank sites at once.
         const size_t site = bwd_workspace_bytes(all_site_problem(p, p.T - 1));
-        return site > 0 && all_wide(p) ? std::max(site, wide_bwd_workspace_bytes(p.N, p.T, p.r))
-                                       : site;
+        return site > 0 && p.mode == LRAR_MODE_SLICED && all_wide(p)
+                   ? std::max(site, wide_bwd_workspace_bytes(p.N, p.T, p.r))
+                   : site;
     }
     return (size_t)all_bwd_workgroups(p.N) * (size_t)p.T * (size_t)p.r * sizeof(float);
 }
@@ -662,7 +664,7 @@ int check_all_bwd_supported(const AllProblem &p, std::string *why)
 int launch_all_bwd(const AllProblem &p, const void *dH, void *dV, void *dK, float *dQ, void *ws,
                    bool accumulate, hipStream_t st, std::string *err)
 {
-    if (all_wide(p))
+    if (all_wide(p) && all_bwd_workspace_bytes(p) >= wide_bwd_workspace_bytes(p.N, p.T, p.r))
         return launch_wide_bwd(p, dH, dV, dQ, ws, accumulate, st, err);
     if (!all_bwd_fused(p)) {
         // Site by site: each site's backward adds into the gradients of its
@@ -680,7 +682,8 @@ int launch_all_bwd(const AllProblem &p, const void *dH, void *dV, void *dK, floa
         for (int64_t j = 0; j < p.T; ++j) {
             const int rc = launch_bwd(all_site_problem(p, j),
                                       static_cast<const char *>(dH) + (size_t)j * p.N * p.d * es,
-                                      dV, dK, dQ + j * p.r, ws, true, st, err);
+                                      dV, dK, dQ + j * p.r, ws, all_bwd_workspace_bytes(p),
+                                      true, st, err);
             if (rc != LRAR_OK)
                 return rc;
         }

@@ -73,8 +73,11 @@ __device__ __forceinline__ bool read_by(const AllArgs &a, int site, int i)
 // scores (-inf past a site's prefix) and the weights (0 there and for absent
 // sites), and writes N_eff if asked for.  STRICT: a NaN or infinite score of
 // a source that the site reads makes the site's weights NaN, as in the
-// single-site kernels; otherwise such a source drops out.
-template <bool STRICT>
+// single-site kernels; otherwise such a source drops out.  Source tiles from
+// NT on hold no source (a compile-time bound that saves their zeros).  GL: the
+// lanes that share a token's sources, col the lane's place among them (fewer
+// than 16 only with one tile).
+template <bool STRICT, int NT = 4, int GL = 16>
 __device__ __forceinline__ void site_softmax(const AllArgs &a, int64_t n, int wave, int col,
                                              int ks, const f32x4_t (&D)[4],
                                              const float (&irho)[4], float (&s)[4][4],
@@ -85,7 +88,7 @@ __device__ __forceinline__ void site_softmax(const AllArgs &a, int64_t n, int wa
 #pragma clang fp contract(off)
     float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
         const int i = 16 * nt + col;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -100,10 +103,10 @@ __device__ __forceinline__ void site_softmax(const AllArgs &a, int64_t n, int wa
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        m[e] = row16_max(m[e]);
+        m[e] = group_max(m[e], GL);
     float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const bool in = STRICT ? read_by(a, 16 * wave + 4 * ks + e, 16 * nt + col)
@@ -113,13 +116,13 @@ __device__ __forceinline__ void site_softmax(const AllArgs &a, int64_t n, int wa
         }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        z[e] = row16_sum(z[e]);
+        z[e] = group_sum(z[e], GL);
     float sa[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const float inv = (STRICT ? z[e] != 0.0f : z[e] > 0.0f) ? 1.0f / z[e] : 0.0f;
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             const bool some = STRICT ? al[nt][e] != 0.0f : al[nt][e] > 0.0f;
             const float ex = al[nt][e];
             al[nt][e] *= inv;
@@ -130,7 +133,7 @@ __device__ __forceinline__ void site_softmax(const AllArgs &a, int64_t n, int wa
     if (a.neff) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            sa[e] = row16_sum(sa[e]);
+            sa[e] = group_sum(sa[e], GL);
             const int site = 16 * wave + 4 * ks + e;
             // STRICT: z exp(-t / z) with the sums of the exponentials, as
             // route_neff forms it (half the error of the other form).
@@ -347,158 +350,52 @@ inline AllArgs all_wide_args(const AllProblem &p)
     return a;
 }
 
+// sum[nt] += A * v[nt]^T over one step of 32 columns, A as TERMS bf16 terms
+// (smallest first).  The step's products start from zero and are then added
+// with an fp32 addition: the matrix cores round a long chain of their own
+// coarsely and downwards (measured 0.6 - 0.9 of 2^-24 a step against 0.3; over
+// rows of 2048 columns dq lost a factor 2 to it).
+template <int TERMS, int NT = 4>
+__device__ __forceinline__ void step_product(const bf16x8_t *A, const u32x4_t (&v)[NT],
+                                             f32x4_t (&sum)[4])
+{
+    f32x4_t t[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+        t[nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < TERMS; ++k)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            t[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                A[k], __builtin_bit_cast(bf16x8_t, v[nt]), t[nt], 0, 0, 0);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+        sum[nt] += t[nt];
+}
+
+// Units of 64 columns that each wave of wide_products takes of `ncol`.
+__device__ __forceinline__ int wide_units(int ncol)
+{
+    return ((ncol + 63) / 64 + kWaves - 1) / kWaves;
+}
+
 // LDS exchange of wide_products, in bytes: one accumulator set per wave.
 template <int MT> constexpr int wide_exchange_bytes() { return kWaves * MT * 4 * kWaveSize * 16; }
 
-// The products of one token that contract whole rows: D = Q [16 MT x r] * K^T
-// [r x 64] (Q as three bf16 terms), and with GRAD also G = dH [16 MT x d] *
-// V^T [d x 64].  On return wave w holds tile w's rows: D[nt], G[nt] of sites
-// 16 w + 4 (l / 16) + e against source 16 nt + (l mod 16); rho_l[nt] = rho of
-// those sources, and rho (LDS, 64 floats) of all.
-// Without GRAD the columns are those of the key; with it those of the whole
-// row, first the ones before the key, then the key's.  The waves share the
-// columns, 64 at a time in turn, so that each line of the token's rows is
-// read once: with a tile of sites per wave, and so every row read by all four,
-// the rows came from beyond the L2 each time (the planes of a stack lie a
-// power of two apart and share the L2's sets) and the backward took 333 us
-// instead of 256 (49 sources, 48 sites, d = 1024, r = 256, 2048 tokens).  The waves'
-// partial sums meet in LDS and are added in wave order.  Steps of 32 columns,
-// AHEAD of them in flight.  No load sits behind a branch, so that the
-// compiler's wait counts leave the later steps in flight: rows past the
-// sources or sites re-read the last one, which reaches only entries that are
-// masked later, and columns past a range's end re-read its last ones against
-// zeros in the other operand.  nsrc: sources that some site reads.
+// The waves' shares of the products, added in wave order: sum k^2 (ss[nt],
+// this lane's columns of source 16 nt + (l mod 16)), then D, then G.  Returns
+// what wide_products does.
 template <int MT, bool GRAD>
-__device__ __forceinline__ void wide_products(const AllArgs &a, int64_t n, const uint16_t *dH,
-                                              int nsrc, unsigned char *exchange, float *rho,
-                                              f32x4_t (&D)[4], f32x4_t (&G)[4], float (&rho_l)[4])
+__device__ __forceinline__ void wide_meet(const AllArgs &a, unsigned char *exchange,
+                                          float (&ss)[4], const f32x4_t (&pd)[MT][4],
+                                          const f32x4_t (&pg)[MT][4], float *rho, f32x4_t (&D)[4],
+                                          f32x4_t (&G)[4], float (&rho_l)[4])
 {
 #pragma clang fp contract(off)
-    // Steps of source rows in flight, and of the sites' rows (which take MT
-    // times the registers: one step, refilled as soon as it has been used,
-    // where two waves per SIMD leave no room for more).
-    constexpr int AHEAD = MT == 1 ? 4 : 2, HA = MT <= 2 ? AHEAD : 1;
     const int lane = threadIdx.x % kWaveSize;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const int lc = lane & 15, ks = lane >> 4;
-    const int key0 = GRAD ? a.koff : 0;  // the key's first column, from `base` on
-    const uint16_t *base = static_cast<const uint16_t *>(a.keys) + n * a.krow + (GRAD ? 0 : a.koff);
-    const size_t plane = (size_t)a.N * a.krow;
-    const uint16_t *rows[4], *hrow[MT];
-    const float *qrow[MT];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-        rows[nt] = base + (size_t)min(16 * nt + lc, nsrc - 1) * plane;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int site = min(16 * mt + lc, a.T - 1);
-        qrow[mt] = a.Q + (size_t)site * a.r - key0;
-        hrow[mt] = GRAD ? dH + ((size_t)site * a.N + n) * a.d : nullptr;
-    }
-    f32x4_t pd[MT][4], pg[MT][4];
-    float ss[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        ss[nt] = 0.0f;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            pd[mt][nt] = pg[mt][nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-
-    // Columns [beg, end), KEY: of the key.
-    auto range = [&](auto keyc, int beg, int end) {
-        constexpr bool KEY = decltype(keyc)::value;
-        u32x4_t v[AHEAD][4], h[HA][MT];
-        f32x4_t q[HA][MT][2];
-        // Column of the wave's step s (this lane's 8).
-        auto column = [&](int s) { return beg + 64 * (wave + kWaves * (s >> 1)) + 32 * (s & 1) + 8 * ks; };
-        auto load_v = [&](int s, int u) {
-            const int c = min(column(s), end - 8);
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-                v[u][nt] = load_raw<uint16_t, 8>(rows[nt] + c);
-        };
-        auto load_h = [&](int s, int u, int mt) {
-            if (GRAD)
-                h[u][mt] = load_raw<uint16_t, 8>(hrow[mt] + min(column(s), end - 8));
-        };
-        auto load_q = [&](int s, int u, int mt) {
-            if (KEY) {
-                const float *p = qrow[mt] + min(column(s), end - 8);
-                q[u][mt][0] = *reinterpret_cast<const f32x4_t *>(p);
-                q[u][mt][1] = *reinterpret_cast<const f32x4_t *>(p + 4);
-            }
-        };
-        auto use = [&](int s, int u) {
-            const bool ok = column(s) < end;
-            if (GRAD) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const bf16x8_t A =
-                        __builtin_bit_cast(bf16x8_t, ok ? h[u % HA][mt] : u32x4_t{0u, 0u, 0u, 0u});
-                    load_h(s + HA, u % HA, mt);
-#pragma unroll
-                    for (int nt = 0; nt < 4; ++nt)
-                        pg[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            A, __builtin_bit_cast(bf16x8_t, v[u][nt]), pg[mt][nt], 0, 0, 0);
-                }
-            }
-            if (KEY) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    float x[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        x[e] = ok ? q[u % HA][mt][e / 4][e % 4] : 0.0f;
-                    bf16x8_t A[3];
-                    split3(x, A[2], A[1], A[0]);
-                    load_q(s + HA, u % HA, mt);
-#pragma unroll
-                    for (int k = 0; k < 3; ++k)
-#pragma unroll
-                        for (int nt = 0; nt < 4; ++nt)
-                            pd[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                A[k], __builtin_bit_cast(bf16x8_t, v[u][nt]), pd[mt][nt], 0, 0, 0);
-                }
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    float y[8], t = 0.0f;
-                    widen(v[u][nt], y);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        t = fmaf(y[e], y[e], t);
-                    ss[nt] += ok ? t : 0.0f;
-                }
-            }
-        };
-        const int units = (end - beg + 63) / 64;
-        const int steps = 2 * ((units - wave + kWaves - 1) / kWaves);
-        if (steps <= 0)
-            return;
-#pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            if (u < HA)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    load_h(u, u, mt);
-                    load_q(u, u, mt);
-                }
-            load_v(u, u);
-        }
-        for (int s = 0; s < steps; s += AHEAD)
-#pragma unroll
-            for (int u = 0; u < AHEAD; ++u) {
-                __builtin_amdgcn_sched_barrier(0);
-                use(s + u, u);
-                __builtin_amdgcn_sched_barrier(0);
-                load_v(s + u + AHEAD, u);
-            }
-    };
-    if (key0 > 0)
-        range(std::false_type{}, 0, key0);
-    range(std::true_type{}, key0, key0 + a.r);
-
-    // The waves' shares, added in wave order: sum k^2, then D, then G.
     f32x4_t *ex = reinterpret_cast<f32x4_t *>(exchange);
     float *exs = reinterpret_cast<float *>(exchange);
 #pragma unroll
@@ -542,11 +439,160 @@ __device__ __forceinline__ void wide_products(const AllArgs &a, int64_t n, const
         meet(pg, G);
 }
 
+// The products of one token that contract whole rows: D = Q [16 MT x r] * K^T
+// [r x 64] (Q as three bf16 terms), and with GRAD also G = dH [16 MT x d] *
+// V^T [d x 64].  On return wave w holds tile w's rows: D[nt], G[nt] of sites
+// 16 w + 4 (l / 16) + e against source 16 nt + (l mod 16); rho_l[nt] = rho of
+// those sources, and rho (LDS, 64 floats) of all.
+// Without GRAD the columns are those of the key; with it those of the whole
+// row, first the ones before the key, then the key's.  The waves share the
+// columns, a run of whole 64-column units each, so that each line of the
+// token's rows is read once: with a tile of sites per wave, and so every row read by all four,
+// the rows came from beyond the L2 each time (the planes of a stack lie a
+// power of two apart and share the L2's sets) and the backward took 333 us
+// instead of 256 (49 sources, 48 sites, d = 1024, r = 256, 2048 tokens).  The waves'
+// partial sums meet in LDS and are added in wave order.  Steps of 32 columns,
+// AHEAD of them in flight.  No load sits behind a branch, so that the
+// compiler's wait counts leave the later steps in flight: rows past the
+// sources or sites re-read the last one, which reaches only entries that are
+// masked later, and columns past a range's end re-read its last ones against
+// zeros in the other operand.  nsrc: sources that some site reads.
+template <int MT, bool GRAD>
+__device__ __forceinline__ void wide_products(const AllArgs &a, int64_t n, const uint16_t *dH,
+                                              int nsrc, unsigned char *exchange, float *rho,
+                                              f32x4_t (&D)[4], f32x4_t (&G)[4], float (&rho_l)[4])
+{
+#pragma clang fp contract(off)
+    // Steps of source rows in flight, and of the sites' rows (which take MT
+    // times the registers: one step, refilled as soon as it has been used,
+    // where two waves per SIMD leave no room for more).  Four steps at MT = 2
+    // and 3 were slower (301 us instead of 239, as above: a wave often has
+    // fewer than eight).
+    constexpr int AHEAD = MT == 1 ? 4 : 2, HA = MT <= 2 ? AHEAD : 1;
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const int lc = lane & 15, ks = lane >> 4;
+    const int key0 = GRAD ? a.koff : 0;  // the key's first column, from `base` on
+    const uint16_t *base = static_cast<const uint16_t *>(a.keys) + n * a.krow + (GRAD ? 0 : a.koff);
+    const size_t plane = (size_t)a.N * a.krow;
+    const uint16_t *rows[4], *hrow[MT];
+    const float *qrow[MT];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+        rows[nt] = base + (size_t)min(16 * nt + lc, nsrc - 1) * plane;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int site = min(16 * mt + lc, a.T - 1);
+        qrow[mt] = a.Q + (size_t)site * a.r - key0;
+        hrow[mt] = GRAD ? dH + ((size_t)site * a.N + n) * a.d : nullptr;
+    }
+    f32x4_t pd[MT][4], pg[MT][4];
+    float ss[4];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        ss[nt] = 0.0f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            pd[mt][nt] = pg[mt][nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    // Columns [beg, end), KEY: of the key.
+    auto range = [&](auto keyc, int beg, int end) {
+        constexpr bool KEY = decltype(keyc)::value;
+        u32x4_t v[AHEAD][4], h[HA][MT];
+        f32x4_t q[HA][MT][2];
+        // The wave's share: `per` units of 64 columns, two steps each.  Column of
+        // its step s (this lane's 8).
+        const int per = wide_units(end - beg);
+        auto column = [&](int s) { return beg + 64 * wave * per + 32 * s + 8 * ks; };
+        auto load_v = [&](int s, int u) {
+            const int c = min(column(s), end - 8);
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                v[u][nt] = load_raw<uint16_t, 8>(rows[nt] + c);
+        };
+        auto load_h = [&](int s, int u, int mt) {
+            if (GRAD)
+                h[u][mt] = load_raw<uint16_t, 8>(hrow[mt] + min(column(s), end - 8));
+        };
+        auto load_q = [&](int s, int u, int mt) {
+            if (KEY) {
+                const float *p = qrow[mt] + min(column(s), end - 8);
+                q[u][mt][0] = *reinterpret_cast<const f32x4_t *>(p);
+                q[u][mt][1] = *reinterpret_cast<const f32x4_t *>(p + 4);
+            }
+        };
+        auto use = [&](int s, int u) {
+            // Past the wave's share (the last round of steps) or the columns.
+            const bool ok = s < 2 * per && column(s) < end;
+            if (GRAD) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const bf16x8_t A =
+                        __builtin_bit_cast(bf16x8_t, ok ? h[u % HA][mt] : u32x4_t{0u, 0u, 0u, 0u});
+                    load_h(s + HA, u % HA, mt);
+                    step_product<1>(&A, v[u], pg[mt]);
+                }
+            }
+            if (KEY) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    float x[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        x[e] = ok ? q[u % HA][mt][e / 4][e % 4] : 0.0f;
+                    bf16x8_t A[3];
+                    split3(x, A[2], A[1], A[0]);
+                    load_q(s + HA, u % HA, mt);
+                    step_product<3>(A, v[u], pd[mt]);
+                }
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt) {
+                    float y[8], t = 0.0f;
+                    widen(v[u][nt], y);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        t = fmaf(y[e], y[e], t);
+                    ss[nt] += ok ? t : 0.0f;
+                }
+            }
+        };
+        // Steps of this wave that hold any column.
+        const int steps = min(2 * per, (end - beg - 64 * wave * per + 31) / 32);
+        if (steps <= 0)
+            return;
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (u < HA)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    load_h(u, u, mt);
+                    load_q(u, u, mt);
+                }
+            load_v(u, u);
+        }
+        for (int s = 0; s < steps; s += AHEAD)
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                __builtin_amdgcn_sched_barrier(0);
+                use(s + u, u);
+                __builtin_amdgcn_sched_barrier(0);
+                load_v(s + u + AHEAD, u);
+            }
+    };
+    if (key0 > 0)
+        range(std::false_type{}, 0, key0);
+    range(std::true_type{}, key0, key0 + a.r);
+
+    wide_meet<MT, GRAD>(a, exchange, ss, pd, pg, rho, D, G, rho_l);
+}
+
 // The softmax gradient of the 16 sites of tile `wave` from the value dots
 // G[nt][e] = dH_j . o_i, in the layout of site_softmax:
 //     ds = alpha (G - sum alpha G),  cq = ds / rho,
 // and skk[nt] = sum over the lane's 4 sites of ds s (the RMSNorm term of the
 // sources' key gradients).  Entries past a site's prefix are 0.
+template <int NT = 4, int GL = 16>
 __device__ __forceinline__ void wide_softmax_grad(const AllArgs &a, int wave, int col, int ks,
                                                   const f32x4_t (&G)[4], const float (&rho_l)[4],
                                                   const float (&s)[4][4],
@@ -555,19 +601,19 @@ __device__ __forceinline__ void wide_softmax_grad(const AllArgs &a, int wave, in
 {
 #pragma clang fp contract(off)
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
         skk[nt] = 0.0f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int site = 16 * wave + 4 * ks + e;
         float gb = 0.0f;
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
             if (read_by(a, site, 16 * nt + col))
                 gb = fmaf(al[nt][e], G[nt][e], gb);
-        gb = row16_sum(gb);
+        gb = group_sum(gb, GL);
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             cq[nt][e] = 0.0f;
             if (read_by(a, site, 16 * nt + col)) {
                 const float ds = al[nt][e] * (G[nt][e] - gb);

@@ -1,6 +1,6 @@
 // Backward of the read sites of a pass for keys wider than kAllMaxRank
-// columns: sliced keys (the last r columns of each value), bf16 storage, S and
-// T up to 64.  The equations
+// columns: sliced keys (the last r columns of each value) and full-rank keys
+// (sliced keys with r = d, of any width), bf16 storage, S and T up to 64.  The equations
 // are those of the all-sites backward of narrow keys; what differs is that a
 // token's keys and queries no longer fit the LDS and the dQ of a token no
 // longer fits the registers of a persistent workgroup, so the work is two
@@ -19,9 +19,20 @@
 //     wave): dQ += cq K over its tokens in registers, on the fp32 matrix
 //     cores, then a fixed-order sum of the shares.
 //
-// Measured (49 sources, 48 sites, d = 1024, sliced r = 256, 2048 tokens; site
-// by site before: 48 x (bwd 77 + dq 5) us): route_all_bwd_wide 239 us (0.61 GB
-// of rows in and out, 0.1 GB of them read twice), wide_dq 34 us, the sum 5 us.
+// The single-site backward of full-rank keys is the same for one site, with
+// its rows in registers (route_bwd_full_rows) and its dQ on the vector units
+// (wide_dq_one): the same operations in the same order for every element of D,
+// G, the softmax, cq and dQ, whichever sites are computed beside it, so that
+// row j of an all-sites dQ is bit for bit the single-site dq of site j (up to
+// the 1024 columns that this form takes).
+//
+// Measured at 49 sources, d = 1024.  48 sites, 2048 tokens: sliced r = 256, 48
+// x (77 + dq 5) us site by site before; now 255 + 44 + 6 us (0.61 GB of rows
+// in and out at least).  Full rank: 48 x (212 + dq 5) us before; now 314 + 130
+// + 5 us: the fp32 matrix cores bound wide_dq, rows read again in part 2 and
+// its short phases the rest.  One full-rank site, 4096 tokens: 447 + 5 us
+// before (two reads of the rows at 256 workgroups); now 204 + 94 + 5 us (0.82
+// GB in and out, then 0.41 GB again for dq).
 #include "route_all_weights.h"
 
 #include <algorithm>
@@ -30,6 +41,9 @@ namespace lrar {
 
 namespace {
 
+constexpr int kDqSlab = 64;                 // key columns per workgroup of the dQ product
+constexpr int kDqAhead = 3;                 // source groups in flight in the dQ product
+constexpr int kDqOneSlab = 256;             // columns per workgroup of the one-site dQ product
 constexpr int kWideSlab = 64;               // columns per wave pass of the value gradient
 constexpr int kOpRow = kAllMaxSources + 8;  // bf16 per LDS row of an operand [source][site]
 
@@ -129,7 +143,7 @@ __global__ __launch_bounds__(kBlock, 2) void route_all_bwd_wide(WideBwdArgs b)
     uint16_t *const chi = alo + kOp, *const clo = chi + kOp;
     __shared__ float rho[kAllMaxSources], ck[kAllMaxSources], part[kWaves * kAllMaxSources];
     const AllArgs &a = b.f;
-    const int64_t n = blockIdx.x;
+    const int64_t n = xcd_block().x;  // each XCD a range of tokens (up to 8% faster)
     const int lane = threadIdx.x % kWaveSize;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const int lc = lane & 15, ks = lane >> 4;
@@ -338,17 +352,262 @@ __global__ __launch_bounds__(kBlock, 2) void route_all_bwd_wide(WideBwdArgs b)
     slabs(std::true_type{}, kslab + wave, nslab);
 }
 
+// The same for one site of full-rank keys (the single-site backward), rows of
+// up to 128 HS columns and up to 16 NT sources: the token's rows stay in
+// registers (a quarter of the row is HS steps of 32 columns), so that every
+// row is read once for the products and the gradient, and the gradient is
+// formed on the vector units (one site would use 1 of 32 rows of the matrix
+// form's contraction).  cq is what route_all_bwd_wide gives for the site, bit
+// for bit: the same products in the same order, quarter by quarter.
+// A token has a workgroup, a quarter of the row per wave (TOK = 0); or, where
+// whole rows of few sources meet many tokens, a wave, which takes the quarters
+// one after the other and needs no exchange (TOK = 1), or a share of a wave
+// (TOK = 2, 4: up to 8, 4 sources; a tile's 16 columns are then the sources of
+// 2, 4 tokens, and row t of the G product is token t's).
+template <int HS, int NT, int TOK, bool ACC>
+__global__ __launch_bounds__(kBlock, 2) void route_bwd_full_rows(WideBwdArgs b)
+{
+#pragma clang fp contract(off)
+    constexpr bool WAVE = TOK > 0;
+    constexpr int P = WAVE ? TOK : 1, GL = 16 / P;  // tokens per wave, lanes per token
+    static_assert(P == 1 || NT == 1, "tokens share one tile of sources");
+    constexpr int QW = WAVE ? kWaves : 1;  // quarters of the row per wave
+    constexpr int kCols = 128 * HS;
+    __shared__ __align__(16) unsigned char exchange[WAVE ? 16 : wide_exchange_bytes<1>()];
+    __shared__ __align__(16) uint16_t hall[(WAVE ? kWaves * P : 1) * kCols];
+    __shared__ __align__(16) float qs[kCols];
+    __shared__ __align__(16) uint16_t qt3[3 * kCols];
+    __shared__ float rho[kAllMaxSources];
+    AllArgs a = b.f;
+    a.T = 1;  // known to the compiler: rows 1 .. 15 of the products fold away
+    a.neff = nullptr;
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const int lc = lane & 15, ks = lane >> 4;
+    // Each XCD a range of tokens (3-5% faster).
+    // The lane's token (the wave's first for P = 1) and its source in a tile;
+    // lanes past the tokens re-read the last one and store nothing.
+    const int tl = lc / GL, il = lc % GL;
+    const int64_t nw = WAVE ? ((int64_t)xcd_block().x * kWaves + wave) * P : xcd_block().x;
+    const bool live = nw + tl < a.N;
+    const int64_t n = min(nw + tl, a.N - 1);
+    uint16_t *const hs = hall + (WAVE ? wave * P * kCols : 0);
+    const size_t plane = (size_t)a.N * a.d;
+    // This lane's columns of step s of quarter k; a quarter has 2 per <= HS
+    // steps (what follows is another quarter's).
+    const int per = wide_units(a.d);
+    auto column = [&](int k, int s) { return 64 * (WAVE ? k : wave) * per + 32 * s + 8 * ks; };
+    const uint16_t *rows[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+        rows[nt] = static_cast<const uint16_t *>(a.V) + n * a.d +
+                   (unsigned)min(16 * nt + il, a.S - 1) * plane;
+    // The upstream row and the query into LDS (all lanes with one ks need the
+    // same 8 columns a step), zeros past the row; their loads go first, so that
+    // the LDS writes don't wait for the rows.
+    constexpr int kHl = WAVE ? (kCols + 4 * kWaveSize - 1) / (4 * kWaveSize) : 1;
+    const int t4 = 4 * threadIdx.x, h4 = WAVE ? 4 * lane : t4;
+    u32x2_t ht[P][kHl];
+    f32x4_t qt = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int t = 0; t < P; ++t)
+#pragma unroll
+        for (int k = 0; k < kHl; ++k) {
+            const int c = h4 + 4 * kWaveSize * k;
+            ht[t][k] = load_raw<uint16_t, 4>(b.dH + min(nw + t, a.N - 1) * a.d + min(c, a.d - 4));
+            if (c >= a.d)
+                ht[t][k] = u32x2_t{0u, 0u};
+        }
+    if (t4 < a.d)
+        qt = *reinterpret_cast<const f32x4_t *>(a.Q + t4);
+    // The lines of a row one after the other, and the two halves of a line
+    // (steps 2 k and 2 k + 1) next to each other here and in the stores: the
+    // planes of a stack often lie a power of two apart, their lines then share
+    // one set of the L2 and don't outlive the other rows of the token (with
+    // the steps outermost and the waves taking columns in turn: 253 us instead
+    // of 202 at 49 sources, d = 1024, 4096 tokens).
+    u32x4_t v[QW][HS][NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int k = 0; k < QW; ++k)
+#pragma unroll
+            for (int s = 0; s < HS; ++s)
+                v[k][s][nt] = load_raw<uint16_t, 8>(rows[nt] + min(column(k, s), a.d - 8));
+#pragma unroll
+    for (int t = 0; t < P; ++t)
+#pragma unroll
+        for (int k = 0; k < kHl; ++k)
+            if (h4 + 4 * kWaveSize * k < kCols)
+                *reinterpret_cast<u32x2_t *>(hs + t * kCols + h4 + 4 * kWaveSize * k) = ht[t][k];
+    if (t4 < kCols) {
+        // The query as it is, for the gradient, and as the products' three
+        // bf16 terms (as split3 forms them), once for all waves and lanes.
+        *reinterpret_cast<f32x4_t *>(qs + t4) = qt;
+        float r[4] = {qt.x, qt.y, qt.z, qt.w};
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            u32x2_t w;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                w[k] = pack_bf16x2(r[2 * k], r[2 * k + 1]);
+                r[2 * k] -= bf16_lo(w[k]);
+                r[2 * k + 1] -= bf16_hi(w[k]);
+            }
+            *reinterpret_cast<u32x2_t *>(qt3 + (2 - t) * kCols + t4) = w;  // smallest first
+        }
+    }
+    lds_barrier();
+    auto query = [&](int c, float (&x)[8]) {
+        const f32x4_t q0 = *reinterpret_cast<const f32x4_t *>(qs + c);
+        const f32x4_t q1 = *reinterpret_cast<const f32x4_t *>(qs + c + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            x[e] = q0[e];
+            x[4 + e] = q1[e];
+        }
+    };
+    f32x4_t D[4], G[4];
+    float rho_l[4];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        D[nt] = G[nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        rho_l[nt] = 0.0f;  // WAVE: sum k^2 at first
+    }
+#pragma unroll
+    for (int k = 0; k < QW; ++k) {
+        f32x4_t pd[1][4], pg[1][4];
+        float ss[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+            pd[0][nt] = pg[0][nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < HS; ++s) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (s >= 2 * per)
+                break;  // wave-uniform
+            const int c = column(k, s);
+            // Row t of the G operand: token t's upstream row.
+            const bf16x8_t Ah =
+                *reinterpret_cast<const bf16x8_t *>(hs + (P > 1 ? lc % P * kCols : 0) + c);
+            step_product<1, NT>(&Ah, v[k][s], pg[0]);
+            bf16x8_t A[3];
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                A[t] = *reinterpret_cast<const bf16x8_t *>(qt3 + t * kCols + c);
+            step_product<3, NT>(A, v[k][s], pd[0]);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                float y[8], t = 0.0f;
+                widen(v[k][s][nt], y);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    t = fmaf(y[e], y[e], t);
+                ss[nt] += c < a.d ? t : 0.0f;
+            }
+        }
+        if constexpr (WAVE) {
+            // The sums of wide_meet, in its order.
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                ss[nt] += __shfl_xor(ss[nt], 16, kWaveSize);
+                ss[nt] += __shfl_xor(ss[nt], 32, kWaveSize);
+                rho_l[nt] += ss[nt];
+                D[nt] = k == 0 ? pd[0][nt] : D[nt] + pd[0][nt];
+                G[nt] = k == 0 ? pg[0][nt] : G[nt] + pg[0][nt];
+            }
+        } else {
+            wide_meet<1, true>(a, exchange, ss, pd, pg, rho, D, G, rho_l);
+        }
+    }
+    if constexpr (WAVE)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            rho_l[nt] = sqrtf(rho_l[nt] / (float)a.r + a.eps);
+    float al_i[NT], cq_i[NT], ck_i[NT];
+    {
+        // Every wave of a token forms the one site's weights and coefficients;
+        // they are on the lanes of row 0 (l < 16), and go to all from there.
+        float s[4][4], al[4][4], cq[4][4], skk[4];
+        if constexpr (P > 1)  // a token's dots are in its own row
+#pragma unroll
+            for (int t = 1; t < P; ++t)
+                G[0][0] = tl == t ? G[0][t] : G[0][0];
+        site_softmax<true, NT, GL>(a, n, 0, il, ks, D, rho_l, s, al);
+        wide_softmax_grad<NT, GL>(a, 0, il, ks, G, rho_l, s, al, cq, skk);
+        if ((WAVE ? live : wave == 0) && ks == 0)
+#pragma unroll
+            for (int k = 0; k < kAllMaxSources / GL; ++k)
+                b.cq[(size_t)n * kAllMaxSources + GL * k + il] = k < NT ? cq[k < NT ? k : 0][0] : 0.0f;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            al_i[nt] = __shfl(al[nt][0], lc, kWaveSize);
+            cq_i[nt] = __shfl(cq[nt][0], lc, kWaveSize);
+            ck_i[nt] = __shfl(skk[nt], lc, kWaveSize) / (rho_l[nt] * rho_l[nt] * (float)a.d);
+        }
+    }
+    // The rows as raw bits again, the query and dH from LDS: what the products
+    // made of them would otherwise be kept for here, in registers that do not
+    // exist.
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int k = 0; k < QW; ++k)
+#pragma unroll
+        for (int s = 0; s < HS; ++s)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                asm volatile("" : "+v"(v[k][s][nt]));
+    // Lane: sources 16 nt + lc, 8 columns a step.
+    uint16_t *d0 = b.dV + n * a.d + (size_t)(unsigned)il * plane;
+#pragma unroll
+    for (int k = 0; k < QW; ++k)
+#pragma unroll
+        for (int s = 0; s < HS; s += 2) {
+            if (s >= 2 * per)
+                break;  // wave-uniform
+            __builtin_amdgcn_sched_barrier(0);
+            float x[2][8], y[2][8];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                query(column(k, s + u), x[u]);
+                widen(*reinterpret_cast<const u32x4_t *>(hs + tl * kCols + column(k, s + u)), y[u]);
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                u32x4_t o[2];
+                uint16_t *dst = d0 + 16 * nt * plane + column(k, s);
+                const bool src = 16 * nt + il < a.S && live;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    float g[8];
+                    widen(v[k][s + u][nt], g);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        g[e] = fmaf(al_i[nt], y[u][e], fmaf(cq_i[nt], x[u][e], -ck_i[nt] * g[e]));
+                    if (ACC && src && column(k, s + u) < a.d)
+                        add_stored(g, load_raw<uint16_t, 8>(dst + 32 * u));
+                    o[u] = Narrow<uint16_t, 8>::run(g);
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (src && column(k, s + u) < a.d)
+                        store_raw<uint16_t, 8>(dst + 32 * u, o[u]);
+            }
+        }
+}
+
 // dQ shares.  Wave `id` of the grid's y dimension sums
 //     share[j][c] = sum_n sum_i cq[n][j][i] k[n][i][c]
-// over its tokens n = id, id + waves, ... in order, for the 128 key columns
-// of slab blockIdx.x, on the fp32 matrix cores: a lane's 16-byte row pieces,
+// over its tokens n = id, id + waves, ... in order (each token's sum on its
+// own, then the tokens': two short chains of fp32 additions instead of one of
+// thousands), for the 64 key columns of slab blockIdx.x, on the fp32 matrix cores: a lane's 8-byte row pieces,
 // widened, are the operands as they stand (16 sources a group, four a step,
 // lane group ks taking sources 4 ks .. 4 ks + 3 of the group, so that its cq
 // come as one 16-byte vector).  The bf16 matrix cores with cq as three terms
-// took 27 us against 34 (49 sources, 48 sites, r = 256, 2048 tokens), but
-// their sums are biased: the error of dQ grew with the tokens, from 1.8e-7 to
-// 3.4e-7 at 2048, where these reach 2.4e-7 (site by site: 2.1e-7).  The 4
-// waves of a workgroup then add up in wave order.
+// took 27 us against 44 (49 sources, 48 sites, r = 256, 2048 tokens), but
+// round long sums coarsely: the error of dQ grew with the tokens, from 1.8e-7
+// to 3.4e-7 at 2048 (site by site 2.1e-7); these stay below the single-site
+// kernels' errors at every number of tokens.  The 4 waves of a workgroup then add up in wave order.
 struct WideDqArgs {
     const uint16_t *V;  // [S][N][d]
     const float *cq;    // [N][T][64]
@@ -360,21 +619,19 @@ struct WideDqArgs {
 // The same share over each site's prefix only, on the vector units (a
 // non-finite source value past a site's prefix met cq = 0).
 __device__ __forceinline__ void wide_dq_prefix(const WideDqArgs &a, int64_t n0, int64_t step,
-                                            int site, int c, float (&v)[8])
+                                            int site, int c, f32x4_t &v)
 {
-#pragma unroll
-    for (int p = 0; p < 8; ++p)
-        v[p] = 0.0f;
+    v = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     const size_t plane = (size_t)a.N * a.d;
 #pragma unroll 1
     for (int64_t n = n0; n < a.N; n += step)
 #pragma unroll 1
         for (int i = 0; i < min(a.S, a.first + site); ++i) {
             const float w = a.cq[((size_t)n * a.T + site) * kAllMaxSources + i];
-            float x[8];
-            widen(load_raw<uint16_t, 8>(a.V + i * plane + n * a.d + (a.d - a.r) + c), x);
+            float x[4];
+            widen(load_raw<uint16_t, 4>(a.V + i * plane + n * a.d + (a.d - a.r) + c), x);
 #pragma unroll
-            for (int p = 0; p < 8; ++p)
+            for (int p = 0; p < 4; ++p)
                 v[p] = fmaf(w, x[p], v[p]);
         }
 }
@@ -382,25 +639,27 @@ __device__ __forceinline__ void wide_dq_prefix(const WideDqArgs &a, int64_t n0, 
 template <int MT>
 __global__ __launch_bounds__(kBlock, 2) void wide_dq(WideDqArgs a)
 {
-    __shared__ __align__(16) float red[16 * kAllSlab * (kWaves - 1)];
+    __shared__ __align__(16) float red[16 * kDqSlab * (kWaves - 1)];
     const int lane = threadIdx.x % kWaveSize;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const int lc = lane & 15, ks = lane >> 4;
-    const int c0 = blockIdx.x * kAllSlab + 8 * lc;
+    const int c0 = blockIdx.x * kDqSlab + 4 * lc;
     const bool ok = c0 < a.r;
     const size_t plane = (size_t)a.N * a.d;
     const uint16_t *key = a.V + (a.d - a.r) + (ok ? c0 : 0);
     const int64_t n0 = (int64_t)blockIdx.y * kWaves + wave, step = (int64_t)gridDim.y * kWaves;
     const int ngroups = (a.S + 15) / 16;
-    f32x4_t acc[MT][8];
+    f32x4_t acc[MT][4], tok[MT][4];  // over the tokens, and of the current one
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int p = 0; p < 8; ++p)
-            acc[mt][p] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    u32x4_t raw[4];
-    f32x4_t q[MT];
-    auto load = [&](int64_t n, int g) {
+        for (int p = 0; p < 4; ++p)
+            acc[mt][p] = tok[mt][p] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    // kDqAhead groups in flight.  A wave's groups in order: those of its first
+    // token, of its next, ...; past the last one, the last again.
+    u32x2_t raw[kDqAhead][4];
+    f32x4_t q[kDqAhead][MT];
+    auto load = [&](int64_t n, int g, int u) {
         // Sources past S re-read the last one; their cq is 0.  Sites past T
         // re-read the last one; their rows are not stored.
         const uint16_t *r0 = key + n * a.d;
@@ -408,54 +667,78 @@ __global__ __launch_bounds__(kBlock, 2) void wide_dq(WideDqArgs a)
         asm volatile("" : "+v"(s0));
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            raw[e] = load_raw<uint16_t, 8>(r0 + (unsigned)min(s0 + e, a.S - 1) * plane);
+            raw[u][e] = load_raw<uint16_t, 4>(r0 + (unsigned)min(s0 + e, a.S - 1) * plane);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-            q[mt] = *reinterpret_cast<const f32x4_t *>(
+            q[u][mt] = *reinterpret_cast<const f32x4_t *>(
                 a.cq + ((size_t)n * a.T + min(16 * mt + lc, a.T - 1)) * kAllMaxSources + 16 * g + 4 * ks);
     };
-    if (n0 < a.N)
-        load(n0, 0);
-    for (int64_t n = n0; n < a.N; n += step)
-        for (int g = 0; g < ngroups; ++g) {
-            u32x4_t now[4];
-            f32x4_t w[MT];
+    auto use = [&](int g, int u) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                now[e] = raw[e];
+        for (int e = 0; e < 4; ++e) {
+            float x[4];
+            widen(raw[u][e], x);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                w[mt] = q[mt];
-            // The next group, or the next token's first (the last again at
-            // the end).
-            const bool more = g + 1 < ngroups;
-            load(more ? n : n + step < a.N ? n + step : n, more ? g + 1 : 0);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int mt = 0; mt < MT; ++mt) {
+                if (16 * g >= a.first + 16 * mt + 15)
+                    continue;  // wave-uniform: no site of the tile reads the group
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float x[8];
-                widen(now[e], x);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    if (16 * g >= a.first + 16 * mt + 15)
-                        continue;  // wave-uniform: no site of the tile reads the group
-#pragma unroll
-                    for (int p = 0; p < 8; ++p)
-                        acc[mt][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[mt][e], x[p], acc[mt][p], 0, 0, 0);
-                }
+                for (int p = 0; p < 4; ++p)
+                    tok[mt][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[u][mt][e], x[p], tok[mt][p], 0, 0, 0);
             }
         }
-    // Lane: sites 16 mt + 4 ks + e, columns c0 .. c0 + 7; one site tile of
+        if (g + 1 == ngroups)  // wave-uniform
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    acc[mt][p] += tok[mt][p];
+                    tok[mt][p] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+    };
+    const int64_t total = n0 < a.N ? ((a.N - n0 + step - 1) / step) * ngroups : 0;
+    int64_t nl = n0;  // token and group of the next load
+    int gl = 0;
+    auto advance = [&]() {
+        if (++gl == ngroups) {
+            gl = 0;
+            nl += step;
+        }
+        if (nl >= a.N) {
+            nl -= step;
+            gl = ngroups - 1;
+        }
+    };
+    if (total > 0) {
+#pragma unroll
+        for (int u = 0; u < kDqAhead; ++u) {
+            load(nl, gl, u);
+            advance();
+        }
+    }
+    int g = 0;
+    for (int64_t k = 0; k < total; k += kDqAhead)
+#pragma unroll
+        for (int u = 0; u < kDqAhead; ++u) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (k + u < total)  // wave-uniform
+                use(g, u);
+            g = g + 1 == ngroups ? 0 : g + 1;
+            __builtin_amdgcn_sched_barrier(0);
+            load(nl, gl, u);
+            advance();
+        }
+    // Lane: sites 16 mt + 4 ks + e, columns c0 .. c0 + 3; one site tile of
     // every wave meets in LDS at a time.
     float *part = a.partial + (size_t)blockIdx.y * a.T * a.r;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        float v[4][8];
+        f32x4_t v[4];
         float bad = 0.0f;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int p = 0; p < 8; ++p) {
+            for (int p = 0; p < 4; ++p) {
                 v[e][p] = acc[mt][p][e];
                 bad = fmaf(v[e][p], 0.0f, bad);
             }
@@ -467,11 +750,9 @@ __global__ __launch_bounds__(kBlock, 2) void wide_dq(WideDqArgs a)
         }
         if (wave > 0)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float *dst = red + ((wave - 1) * 16 + 4 * ks + e) * kAllSlab + 8 * lc;
-                *reinterpret_cast<f32x4_t *>(dst) = f32x4_t{v[e][0], v[e][1], v[e][2], v[e][3]};
-                *reinterpret_cast<f32x4_t *>(dst + 4) = f32x4_t{v[e][4], v[e][5], v[e][6], v[e][7]};
-            }
+            for (int e = 0; e < 4; ++e)
+                *reinterpret_cast<f32x4_t *>(red + ((wave - 1) * 16 + 4 * ks + e) * kDqSlab + 4 * lc) =
+                    v[e];
         __syncthreads();
         if (wave == 0 && ok)
 #pragma unroll
@@ -480,17 +761,111 @@ __global__ __launch_bounds__(kBlock, 2) void wide_dq(WideDqArgs a)
                 if (site >= a.T)
                     continue;
 #pragma unroll
-                for (int w = 0; w < kWaves - 1; ++w) {
-                    const float *src = red + (w * 16 + 4 * ks + e) * kAllSlab + 8 * lc;
-#pragma unroll
-                    for (int p = 0; p < 8; ++p)
-                        v[e][p] += src[p];
-                }
-                float *dst = part + (size_t)site * a.r + c0;
-                *reinterpret_cast<f32x4_t *>(dst) = f32x4_t{v[e][0], v[e][1], v[e][2], v[e][3]};
-                *reinterpret_cast<f32x4_t *>(dst + 4) = f32x4_t{v[e][4], v[e][5], v[e][6], v[e][7]};
+                for (int w = 0; w < kWaves - 1; ++w)
+                    v[e] += *reinterpret_cast<const f32x4_t *>(red + (w * 16 + 4 * ks + e) * kDqSlab + 4 * lc);
+                *reinterpret_cast<f32x4_t *>(part + (size_t)site * a.r + c0) = v[e];
             }
         __syncthreads();
+    }
+}
+
+// The shares of one site, on the vector units: the matrix form would use one
+// of its 16 rows, and is then bound by the matrix cores (110 us instead of
+// 82 at 49 sources, d = r = 1024, 4096 tokens).  The same operations in the same order:
+// v_mfma_f32_16x16x4_f32 is a chain of four fused multiply-adds, k ascending
+// (measured against such chains, bit for bit), here sources 16 g + e, + 4,
+// + 8, + 12 for e = 0 .. 3.  A lane owns 4 columns; AHEAD groups in flight.  K4: the
+// fours of sources that a group holds (4, or fewer where S <= 8 leaves one
+// group mostly empty; cq is 0 there).
+template <int K4>
+__global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
+{
+    constexpr int AHEAD = 8 / K4;
+    __shared__ __align__(16) float red[(kWaves - 1) * kDqOneSlab];
+    const BlockXY blk = xcd_block();  // the slabs of one share on one XCD
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const int c0 = blk.x * kDqOneSlab + 4 * lane;
+    const bool ok = c0 < a.r;
+    const size_t plane = (size_t)a.N * a.d;
+    const uint16_t *key = a.V + (a.d - a.r) + (ok ? c0 : 0);
+    const int64_t n0 = (int64_t)blk.y * kWaves + wave, step = (int64_t)gridDim.y * kWaves;
+    const int ngroups = (a.S + 15) / 16;
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, tok[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    u32x2_t raw[AHEAD][4 * K4];
+    auto load = [&](int64_t n, int g, int u) {
+        const uint16_t *r0 = key + n * a.d;
+#pragma unroll
+        for (int i = 0; i < 4 * K4; ++i)  // sources past S re-read the last one; their cq is 0
+            raw[u][i] = load_stream<uint16_t, 4, true>(r0 + (size_t)min(16 * g + i, a.S - 1) * plane);
+    };
+    auto use = [&](int64_t n, int g, int u) {
+        const float *c = a.cq + (size_t)n * kAllMaxSources + 16 * g;  // wave-uniform
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int k = 0; k < K4; ++k) {
+                float x[4];
+                widen(raw[u][4 * k + e], x);
+                const float w = c[4 * k + e];
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    tok[p] = fmaf(w, x[p], tok[p]);
+            }
+        if (g + 1 == ngroups)  // wave-uniform
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                acc[p] += tok[p];
+                tok[p] = 0.0f;
+            }
+    };
+    const int64_t total = n0 < a.N ? ((a.N - n0 + step - 1) / step) * ngroups : 0;
+    int64_t nl = n0, nu = n0;  // token and group of the next load and of the next use
+    int gl = 0, gu = 0;
+    auto advance = [&]() {
+        if (++gl == ngroups) {
+            gl = 0;
+            nl += step;
+        }
+        if (nl >= a.N) {
+            nl -= step;
+            gl = ngroups - 1;
+        }
+    };
+    if (total > 0) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            load(nl, gl, u);
+            advance();
+        }
+    }
+    for (int64_t k = 0; k < total; k += AHEAD)
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (k + u < total) {  // wave-uniform
+                use(nu, gu, u);
+                if (++gu == ngroups) {
+                    gu = 0;
+                    nu += step;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load(nl, gl, u);
+            advance();
+        }
+    if (wave > 0)
+        *reinterpret_cast<f32x4_t *>(red + (wave - 1) * kDqOneSlab + 4 * lane) =
+            f32x4_t{acc[0], acc[1], acc[2], acc[3]};
+    __syncthreads();
+    if (wave == 0 && ok) {
+#pragma unroll
+        for (int w = 0; w < kWaves - 1; ++w)
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                acc[p] += red[w * kDqOneSlab + 4 * lane + p];
+        *reinterpret_cast<f32x4_t *>(a.partial + (size_t)blk.y * a.r + c0) =
+            f32x4_t{acc[0], acc[1], acc[2], acc[3]};
     }
 }
 
@@ -540,23 +915,33 @@ __global__ __launch_bounds__(kBlock) void wide_dq_sum(const float *__restrict__ 
 
 template <int MT>
 void launch_wide_mt(const WideBwdArgs &b, const WideDqArgs &q, dim3 qgrid, bool accumulate,
-                    hipStream_t st)
+                    bool rows, hipStream_t st)
 {
     const dim3 grid((unsigned)b.f.N), block(kBlock);
-    if (accumulate)
-        hipLaunchKernelGGL((route_all_bwd_wide<MT, true>), grid, block, 0, st, b);
+    if (!rows) {
+        if (accumulate)
+            hipLaunchKernelGGL((route_all_bwd_wide<MT, true>), grid, block, 0, st, b);
+        else
+            hipLaunchKernelGGL((route_all_bwd_wide<MT, false>), grid, block, 0, st, b);
+    }
+    const dim3 one((unsigned)((q.r + kDqOneSlab - 1) / kDqOneSlab), qgrid.y);
+    if (q.T == 1 && q.S <= 4)
+        hipLaunchKernelGGL(wide_dq_one<1>, one, block, 0, st, q);
+    else if (q.T == 1 && q.S <= 8)
+        hipLaunchKernelGGL(wide_dq_one<2>, one, block, 0, st, q);
+    else if (q.T == 1)
+        hipLaunchKernelGGL(wide_dq_one<4>, one, block, 0, st, q);
     else
-        hipLaunchKernelGGL((route_all_bwd_wide<MT, false>), grid, block, 0, st, b);
-    hipLaunchKernelGGL(wide_dq<MT>, qgrid, block, 0, st, q);
+        hipLaunchKernelGGL(wide_dq<MT>, qgrid, block, 0, st, q);
 }
 
-// Token shares of wide_dq: about two workgroups per CU over all key slabs,
+// Token shares of wide_dq: about four workgroups per CU over all key slabs,
 // at least one token per wave.  Depends on N and r only (not on the sites or
 // sources), so that the order of every dQ sum does too.
 int64_t wide_shares(int64_t N, int64_t r)
 {
-    const int64_t nslab = (r + kAllSlab - 1) / kAllSlab;
-    return std::max<int64_t>(1, std::min<int64_t>(512 / nslab, (N + kWaves - 1) / kWaves));
+    const int64_t nslab = (r + kDqSlab - 1) / kDqSlab;
+    return std::max<int64_t>(1, std::min<int64_t>(1024 / nslab, (N + kWaves - 1) / kWaves));
 }
 
 }  // namespace
@@ -566,6 +951,69 @@ size_t wide_bwd_workspace_bytes(int64_t N, int64_t T, int64_t r)
 {
     return 16 + ((size_t)N * T * kAllMaxSources + (size_t)wide_shares(N, r) * T * r) * sizeof(float);
 }
+
+namespace {
+
+// Tokens above which few sources take a wave per token: the quarters of its
+// rows then run one after the other, which costs a call of few tokens more
+// than the idle lanes of a workgroup per token do.
+constexpr int64_t kFullWaveTokens = 2048;
+
+template <int HS, int NT, int TOK, bool ACC>
+void launch_rows(const WideBwdArgs &b, hipStream_t st)
+{
+    constexpr int per = TOK > 0 ? TOK * kWaves : 1;  // tokens per workgroup
+    hipLaunchKernelGGL((route_bwd_full_rows<HS, NT, TOK, ACC>),
+                       dim3((unsigned)((b.f.N + per - 1) / per)), dim3(kBlock), 0, st, b);
+}
+
+// HS for the row width; a wave holds at most 32 vectors a lane of its rows, so
+// a whole token's (4 HS NT) only where these are as few.
+template <int HS, bool ACC>
+void launch_rows_hs(const WideBwdArgs &b, hipStream_t st)
+{
+    const int nt = (b.f.S + 15) / 16;
+    const bool many = b.f.N > kFullWaveTokens;
+    if (many && b.f.S <= 4)
+        return launch_rows<HS, 1, 4, ACC>(b, st);
+    if (many && b.f.S <= 8)
+        return launch_rows<HS, 1, 2, ACC>(b, st);
+    if (many && nt == 1)
+        return launch_rows<HS, 1, 1, ACC>(b, st);
+    if constexpr (HS <= 4)
+        if (many && nt == 2)
+            return launch_rows<HS, 2, 1, ACC>(b, st);
+    if constexpr (HS <= 2) {
+        if (many)
+            return launch_rows<HS, 4, 1, ACC>(b, st);
+    } else {
+        if (nt == 2)
+            return launch_rows<HS, 2, 0, ACC>(b, st);
+        if (nt == 3)
+            return launch_rows<HS, 3, 0, ACC>(b, st);
+    }
+    launch_rows<HS, 4, 0, ACC>(b, st);
+}
+
+// The single site of full-rank keys with its rows in registers, up to
+// kFullRowsMax columns; false for others, which the all-sites kernel takes (wider rows
+// don't fit the registers; there it reads them twice).
+template <bool ACC>
+bool launch_full_rows(const WideBwdArgs &b, hipStream_t st)
+{
+    const AllArgs &a = b.f;
+    if (a.T != 1 || a.koff != 0 || a.S != b.sources || a.d > kFullRowsMax)
+        return false;
+    if (a.d <= 256)
+        launch_rows_hs<2, ACC>(b, st);
+    else if (a.d <= 512)
+        launch_rows_hs<4, ACC>(b, st);
+    else
+        launch_rows_hs<8, ACC>(b, st);
+    return true;
+}
+
+}  // namespace
 
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
                     bool accumulate, hipStream_t st, std::string *err)
@@ -584,12 +1032,13 @@ int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, vo
         b.cq = cq;
         const WideDqArgs q{static_cast<const uint16_t *>(p.V), cq, partial, b.f.S, (int)p.d,
                            (int)p.r, b.f.first, b.f.T, p.N};
-        const dim3 qgrid((unsigned)((p.r + kAllSlab - 1) / kAllSlab), (unsigned)shares);
+        const dim3 qgrid((unsigned)((p.r + kDqSlab - 1) / kDqSlab), (unsigned)shares);
+        const bool rows = accumulate ? launch_full_rows<true>(b, st) : launch_full_rows<false>(b, st);
         switch ((b.f.T + 15) / 16) {
-        case 1: launch_wide_mt<1>(b, q, qgrid, accumulate, st); break;
-        case 2: launch_wide_mt<2>(b, q, qgrid, accumulate, st); break;
-        case 3: launch_wide_mt<3>(b, q, qgrid, accumulate, st); break;
-        default: launch_wide_mt<4>(b, q, qgrid, accumulate, st); break;
+        case 1: launch_wide_mt<1>(b, q, qgrid, accumulate, rows, st); break;
+        case 2: launch_wide_mt<2>(b, q, qgrid, accumulate, rows, st); break;
+        case 3: launch_wide_mt<3>(b, q, qgrid, accumulate, rows, st); break;
+        default: launch_wide_mt<4>(b, q, qgrid, accumulate, rows, st); break;
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)

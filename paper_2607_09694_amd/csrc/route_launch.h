@@ -28,6 +28,8 @@ int check_supported(const Problem &p, bool bwd, std::string *why);
 
 // Workspace of the backward (per-workgroup dq partials).  No HIP call.
 size_t bwd_workspace_bytes(const Problem &p);
+// The dq partials alone (what every form but full rank's matrix-core one needs).
+size_t bwd_partial_bytes(const Problem &p);
 
 int launch_fwd(const Problem &p, void *H, hipStream_t st, std::string *err);
 // Online-softmax states of the sources in chunks of `chunk` (see
@@ -38,8 +40,10 @@ int launch_state(const Problem &p, int64_t chunk, float *M, float *L, float *ACC
 int launch_merge(const float *M, const float *L, const float *ACC, int64_t P, int64_t N, int64_t d,
                  int dtype, void *H, hipStream_t st, std::string *err);
 // accumulate: add the gradients into dV, dK and dq instead of overwriting.
+// ws_bytes: full-rank keys take the matrix-core form where it holds that
+// form's workspace, which bwd_workspace_bytes(p) always does.
 int launch_bwd(const Problem &p, const void *dH, void *dV, void *dK, float *dq, void *ws,
-               bool accumulate, hipStream_t st, std::string *err);
+               size_t ws_bytes, bool accumulate, hipStream_t st, std::string *err);
 
 // Largest dq-partial workspace the allocation-free backward serves from its
 // file-scope device array (8 MiB per device).
@@ -169,6 +173,8 @@ bool all_fused(const AllProblem &p);
 bool all_wide(const AllProblem &p);
 // Their backward; the workspace is 4-byte aligned, dK does not exist.
 size_t wide_bwd_workspace_bytes(int64_t N, int64_t T, int64_t r);
+// Widest full-rank row that the single-site form keeps in registers.
+constexpr int64_t kFullRowsMax = 1024;
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
                     bool accumulate, hipStream_t st, std::string *err);
 // The single-site problem of site j of an all-sites problem.

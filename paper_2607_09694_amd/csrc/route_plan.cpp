@@ -3,6 +3,8 @@
 // Host code only.
 #include "route_common.h"
 
+#include <algorithm>
+
 namespace lrar {
 
 namespace {
@@ -128,7 +130,7 @@ int check_supported(const Problem &p, bool bwd, std::string *why)
     return make_plan(p, bwd, &pl, why) ? LRAR_OK : LRAR_EUNSUPPORTED;
 }
 
-size_t bwd_workspace_bytes(const Problem &p)
+size_t bwd_partial_bytes(const Problem &p)
 {
     Plan pl;
     std::string why;
@@ -136,6 +138,19 @@ size_t bwd_workspace_bytes(const Problem &p)
         return 0;
     const int64_t ncols = p.mode == LRAR_MODE_FULL ? p.d : p.r;
     return (size_t)pl.nblocks * (size_t)ncols * sizeof(float);
+}
+
+size_t bwd_workspace_bytes(const Problem &p)
+{
+    // Full rank: enough for every site of a pass that ends with this one, so
+    // that the single-site and the all-sites call share one size (S sites at
+    // most).  Also where S is past what the matrix-core form takes: the first
+    // sites of such a pass take it.  One source never does (its weight is 1
+    // and its dq 0).
+    const size_t need = bwd_partial_bytes(p);
+    const bool wide = p.mode == LRAR_MODE_FULL && p.dtype == LRAR_DTYPE_BF16 && p.d % 8 == 0 &&
+                      p.S > 1;
+    return need > 0 && wide ? std::max(need, wide_bwd_workspace_bytes(p.N, std::min<int64_t>(p.S, 64), p.d)) : need;
 }
 
 }  // namespace lrar

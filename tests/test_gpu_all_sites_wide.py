@@ -1,4 +1,4 @@
-"""GPU parity of the all-sites calls with sliced keys wider than 64 columns
+"""GPU parity of the all-sites calls with full-rank keys and with sliced keys wider than 64 columns
 (bf16 storage), forward and backward, against the fp64 oracle: one to four
 site tiles and source tiles, keys that end inside a 32-column step or start
 inside one, ragged slabs, sources that no site reads, one token and more
@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import paper_2607_09694_amd as lr
-from paper_2607_09694_amd.inputs import SLICED, bf16_bits_from_f32, f32_from_bf16_bits, \
+from paper_2607_09694_amd.inputs import FULL, SLICED, bf16_bits_from_f32, f32_from_bf16_bits, \
     make_host_problem
 from parity import check_bf16_grown, check_bf16_key_grad, check_bf16_value, check_dq, check_f32
 from test_gpu_all_sites_bwd import _queries, _upstream, dev, to_dev, to_host  # noqa: F401
@@ -117,3 +117,57 @@ def test_wide_keys_confine_non_finite_values(dev, value, column):  # noqa: F811
     assert torch.allclose(dV[first:].float(), dV0[first:].float(), rtol=2.0 ** -7, atol=1e-4)
     assert not bool(torch.isfinite(dV[:first, 2, column].float()).any())
     assert torch.allclose(dQ[1:], dQ0[1:], rtol=1e-4, atol=1e-4)
+
+
+# Full-rank keys: (S, T, first, N, d).  Every width of the single-site kernel
+# that keeps its rows in registers (256, 512, 1024 columns, ragged), rows wider
+# than those, and more tokens than run site by site in the forward.
+FULL_CASES = [(33, 20, 3, 9, 200), (12, 11, 2, 5, 488), (49, 48, 2, 6, 1000), (9, 8, 2, 6, 1544),
+              (18, 3, 16, 1030, 136)]
+# (S, N, d) of single sites with many tokens: a wave per token, or per 2 or 4.
+MANY_TOKENS = [(2, 2051, 1000), (4, 2049, 136), (7, 2050, 512), (16, 2053, 776), (30, 2049, 264),
+               (64, 2049, 96)]
+
+
+@pytest.mark.parametrize("case", FULL_CASES, ids=lambda c: "S{}-T{}-f{}-N{}-d{}".format(*c))
+def test_full_rank_sites_match_oracle_and_single_sites(dev, case):  # noqa: F811
+    S, T, first, N, d = case
+    p, Q, dH, V, Qd, dHd = _run(dev, (S, T, first, N, d, d), seed=S + T + N)
+    Q64 = Q.astype(np.float64)
+    dV, _, dQ = lr.route_all_bwd(V, None, Qd, dHd, FULL, first)
+    H, ne = lr.route_all_fwd(V, None, Qd, FULL, first)
+    torch.cuda.synchronize()
+    Hr, NEr = oracle.route_all_fwd(p.V, None, Q64, FULL, first, r=d)
+    rV, _, rQ = oracle.route_all_bwd(p.V, None, Q64, dH, FULL, first, r=d)
+    check_bf16_value("H", to_host(H), Hr)
+    check_f32("neff", to_host(ne), NEr)
+    check_bf16_key_grad("dV", to_host(dV), rV)
+    check_dq("dQ", to_host(dQ), rQ)
+    for j in sorted({0, T // 2, T - 1}):
+        sV, _, sq = lr.route_bwd(V[:first + j], None, Qd[j].contiguous(), dHd[j], FULL)
+        torch.cuda.synchronize()
+        if d <= 1024:
+            assert torch.equal(dQ[j], sq), f"dQ row {j}"
+        oV, _, _ = oracle.route_bwd(p.V[:first + j], None, Q64[j], dH[j], FULL, r=d)
+        check_bf16_value("single-site dV", to_host(sV), oV)
+
+
+@pytest.mark.parametrize("case", MANY_TOKENS, ids=lambda c: "S{}-N{}-d{}".format(*c))
+@pytest.mark.parametrize("accumulate", [False, True], ids=["write", "add"])
+def test_full_rank_single_site_of_many_tokens(dev, case, accumulate):  # noqa: F811
+    S, N, d = case
+    p, Q, dH, V, Qd, dHd = _run(dev, (S, 1, S, N, d, d), seed=S + N)
+    rV, _, rQ = oracle.route_bwd(p.V, None, Q[0].astype(np.float64), dH[0], FULL, r=d)
+    out = None
+    if accumulate:
+        dV0 = bf16_bits_from_f32(np.random.default_rng(5).standard_normal((S, N, d)).astype(np.float32))
+        out = (to_dev(dV0, dev), None, torch.zeros((d,), device=dev))
+        rV = rV + f32_from_bf16_bits(dV0)
+    dV, _, dq = lr.route_bwd(V, None, Qd[0].contiguous(), dHd[0], FULL, out=out, accumulate=accumulate)
+    _, _, dQ = lr.route_all_bwd(V, None, Qd, dHd, FULL, S)
+    torch.cuda.synchronize()
+    # Few sources leave |dV| past 5.12, where a correctly rounded bf16 is up to
+    # 2^-8 |dV| off: the bar for grown values.
+    check_bf16_grown("dV", to_host(dV), rV)
+    check_dq("dq", to_host(dq), rQ)
+    assert torch.equal(dQ[0], dq)
