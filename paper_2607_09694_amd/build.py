@@ -11,7 +11,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "liblrattnres.so")
-SOURCES = ["route_fwd.hip", "route_bwd.hip", "route_block.hip", "route_all.hip",
+SOURCES = ["route_fwd.hip", "route_bwd.hip", "route_bwd_defer.hip", "route_block.hip", "route_all.hip",
            "route_all_bwd.hip", "route_all_wide.hip", "key_proj.hip", "key_proj_bwd.hip", "route_plan.cpp", "capi.cpp"]
 # Benchmark-only helper: streaming copy / read kernels of known traffic.
 PROBE_LIB = os.path.join(PKG, "libhbmprobe.so")

@@ -89,6 +89,9 @@ template <int NCH> struct MixUnroll { static constexpr int value = NCH >= 8 ? 1 
 template <int NCH> struct BwdInflight {
     static constexpr int value = NCH >= 8 ? 1 : NCH == 4 ? LRAR_BWD_INFLIGHT_WIDE : NCH >= 2 ? 2 : 4;
 };
+// The same where a workgroup shares one token (few tokens, latency-bound): all
+// that the registers of two waves per SIMD hold.
+template <int NCH> struct BwdInflightSplit { static constexpr int value = NCH >= 8 ? 2 : NCH == 4 ? 4 : 8; };
 // Cache policy of the backward's value-row loads and gradient-row stores.
 #ifndef LRAR_BWD_NT_LOAD
 #define LRAR_BWD_NT_LOAD 1
@@ -526,11 +529,13 @@ struct Plan {
     int s_pad = 4;
     int r_pad = 4;
     size_t lds = 0;
-    bool wg_split = false;  // forward: the sources of a token split over a workgroup
+    bool wg_split = false;  // the sources of a token split over a workgroup (few tokens)
 };
 
 // Fills *pl for a validated problem, or returns false with the reason.
-bool make_plan(const Problem &p, bool bwd, Plan *pl, std::string *why);
+// split: a backward of few tokens may split each token's sources over a
+// workgroup (not for block sources).
+bool make_plan(const Problem &p, bool bwd, Plan *pl, std::string *why, bool split = true);
 
 // Switches a forward plan to one token per workgroup, its sources split
 // over the waves (route_fwd_lr_wg, route_fwd_full_1p<kFullWg>), when the

@@ -25,6 +25,12 @@ constexpr int64_t kWgSplitLowRank = 2048;
 constexpr int64_t kWgSplitFull = 1024;
 #endif
 
+// Tokens up to which the low-rank backward splits each token's sources over a
+// workgroup.  Step of forward and backward, one wave per token -> split: 49
+// sources, d = 1024, r = 16: 46 -> 27 us at 128 tokens, 52 -> 39 at 512, 67 ->
+// 68 at 1024; 64 sources, d = 2048: 81 -> 39, 103 -> 91, 146 -> 156.
+constexpr int64_t kWgSplitBwd = 512;
+
 // Workgroups below which a backward gives its waves fewer tokens (two per CU).
 constexpr int64_t kFewBlocks = 512;
 
@@ -46,7 +52,7 @@ void plan_wg_split(const Problem &p, Plan *pl)
     pl->lds = (scores + 2 * kWaves + (kWaves - 1) * row) * sizeof(float);
 }
 
-bool make_plan(const Problem &p, bool bwd, Plan *pl, std::string *why)
+bool make_plan(const Problem &p, bool bwd, Plan *pl, std::string *why, bool split)
 {
     const int vmax = p.dtype == LRAR_DTYPE_BF16 ? 8 : 4;
     pl->vec = p.d % vmax == 0 ? vmax : 1;
@@ -105,7 +111,10 @@ bool make_plan(const Problem &p, bool bwd, Plan *pl, std::string *why)
                (p.N / (kWaves * (pl->tpw / 2)) + 1) * ncols * (int64_t)sizeof(float) <=
                    (int64_t)kNoAllocScratchBytes)
             pl->tpw /= 2;
-        const int64_t per_block = (int64_t)kWaves * pl->tpw;
+        pl->wg_split = split && p.mode != LRAR_MODE_FULL && p.S >= 2 && p.N <= kWgSplitBwd;
+        const int64_t per_block = pl->wg_split ? 1 : (int64_t)kWaves * pl->tpw;
+        if (pl->wg_split)
+            pl->tpw = 1;
         pl->nblocks = (int)((p.N + per_block - 1) / per_block);
         pl->lds = (size_t)kWaves * 4 * pl->s_pad * sizeof(float);
         pl->lds += p.mode == LRAR_MODE_FULL ? (size_t)round_up((int)p.d, 4) * sizeof(float)
