@@ -303,6 +303,159 @@ __global__ __launch_bounds__(kPThreads, 1) void key_proj_gemm(ProjArgs a)
         key_proj_tile<9>(a, lds, n0, j0, width, half);
 }
 
+// ---------------------------------------------------------------------------
+// Few tokens.  A 256 x 256 tile per workgroup leaves a decoding batch on a
+// handful of CUs, each walking the whole of k alone (30 us at 64 tokens,
+// m = d = 1024, on 4 workgroups).  Here a workgroup takes 16 RT tokens x 16 CT
+// output columns and its four waves a quarter of k each, with operand
+// fragments straight from memory (both are k-contiguous; what several
+// workgroups read comes from the L2) and kFewAhead steps of 32 in flight; the
+// partial sums meet in LDS and add up in wave order.
+// ---------------------------------------------------------------------------
+constexpr int kFewWaves = 4, kFewThreads = kFewWaves * kWaveSize, kFewAhead = 4;
+
+template <int RT, int CT>
+__global__ __launch_bounds__(kFewThreads, 2) void key_proj_few(ProjArgs a)
+{
+    constexpr int kRows = 16 * RT, kCols = 16 * CT, kLdsRow = kCols + 4;
+    __shared__ __align__(16) float part[kFewWaves * kRows * kLdsRow];
+    const int tid = threadIdx.x;
+    const int lane = tid % kWaveSize, wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
+    const int fr = lane & 15, fq = lane >> 4;
+    const int nout = a.d + a.r;
+    const int64_t n0 = (int64_t)blockIdx.y * kRows;
+    const int j0 = blockIdx.x * kCols;
+    // The wave's k range, in whole steps; rows and columns past the ends
+    // re-read the last one and are not stored.
+    const int per = (a.m + 32 * kFewWaves - 1) / (32 * kFewWaves) * 32;
+    const int kbeg = min(wave * per, a.m), kend = min(kbeg + per, a.m);
+    const uint16_t *ap[RT], *wp[CT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+        ap[i] = a.A + min(n0 + 16 * i + fr, a.N - 1) * a.m;
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+        wp[j] = a.W + (size_t)min(j0 + 16 * j + fr, nout - 1) * a.m;
+    u32x4_t av[kFewAhead][RT], wv[kFewAhead][CT];
+    auto load = [&](int k0, int u) {
+        const int k = min(k0 + 8 * fq, a.m - 8);
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+            av[u][i] = load_raw<uint16_t, 8>(ap[i] + k);
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+            wv[u][j] = load_raw<uint16_t, 8>(wp[j] + k);
+    };
+    f32x4_t acc[RT][CT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+            acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int u = 0; u < kFewAhead; ++u)
+        load(kbeg + 32 * u, u);
+    for (int k0 = kbeg; k0 < kend; k0 += 32 * kFewAhead)
+#pragma unroll
+        for (int u = 0; u < kFewAhead; ++u) {
+            __builtin_amdgcn_sched_barrier(0);
+            const int k = k0 + 32 * u;
+            if (k + 32 > kend) {  // wave-uniform: past the wave's range
+                const bool ok = k + 8 * fq < kend;
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+                    av[u][i] = ok ? av[u][i] : u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int j = 0; j < CT; ++j)
+                    wv[u][j] = ok ? wv[u][j] : u32x4_t{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int j = 0; j < CT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8_t, av[u][i]), __builtin_bit_cast(bf16x8_t, wv[u][j]),
+                        acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            load(k + 32 * kFewAhead, u);
+        }
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                part[(wave * kRows + 16 * i + 4 * fq + e) * kLdsRow + 16 * j + fr] = acc[i][j][e];
+    __syncthreads();
+    for (int f = tid; f < kRows * (kCols / 8); f += kFewThreads) {
+        const int row = f / (kCols / 8), c = 8 * (f % (kCols / 8));
+        const int64_t n = n0 + row;
+        if (n >= a.N)
+            continue;
+        float v[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w = 0; w < kFewWaves; ++w) {
+            const float *p = part + (w * kRows + row) * kLdsRow + c;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                v[e] += p[e];
+        }
+        const u32x4_t o = Narrow<uint16_t, 8>::run(v);
+        const int j = j0 + c;
+        if (j + 8 <= a.d && a.ovec) {
+            store_raw<uint16_t, 8>(a.O + n * a.d + j, o);
+        } else if (j >= a.d && j + 8 <= nout && a.kvec) {
+            store_raw<uint16_t, 8>(a.K + n * a.r + (j - a.d), o);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int col = j + e;
+                const uint16_t x = (uint16_t)(o[e / 2] >> (16 * (e & 1)));
+                if (col < a.d)
+                    a.O[n * a.d + col] = x;
+                else if (col < nout)
+                    a.K[n * a.r + (col - a.d)] = x;
+            }
+        }
+    }
+}
+
+template <int RT, int CT>
+void launch_few_tile(const ProjArgs &a, hipStream_t st)
+{
+    const dim3 grid((unsigned)((a.d + a.r + 16 * CT - 1) / (16 * CT)),
+                    (unsigned)((a.N + 16 * RT - 1) / (16 * RT)));
+    hipLaunchKernelGGL((key_proj_few<RT, CT>), grid, dim3(kFewThreads), 0, st, a);
+}
+
+// Measured, 256 x 256 tiles -> few-token tiles (d = 1024 unless said): m = 1024:
+// 30 -> 9.6 us at 1 to 128 tokens, 32 -> 24 at 1024; m = 2816: 70 -> 17 at 64,
+// 73 -> 51 at 1024; m = 4096, d = 2048: 100 -> 21 at 64, 103 -> 91 at 1024 (528
+// tiles of 64 x 64); at 2048 tokens (544 tiles) 33 -> 35 and 76 -> 77.  So the
+// line lies at the number of 64 x 64 tiles, about two per CU.
+constexpr int64_t kFewTiles = 528;
+// 64 columns a workgroup from this many tiles on (m = 2816, 256 tokens, 68
+// tiles: 31 -> 26 us); 16 below, where more workgroups count for more than
+// reading the tokens' rows less often (64 tokens, 17 tiles).
+constexpr int64_t kFewWide = 64;
+
+int64_t few_tiles(const ProjArgs &a)
+{
+    return (int64_t)((a.d + a.r + 63) / 64) * ((a.N + 63) / 64);
+}
+
+void launch_few(const ProjArgs &a, hipStream_t st)
+{
+    if (few_tiles(a) >= kFewWide)
+        launch_few_tile<4, 4>(a, st);
+    else if (a.N <= 16)
+        launch_few_tile<1, 1>(a, st);
+    else if (a.N <= 32)
+        launch_few_tile<2, 1>(a, st);
+    else
+        launch_few_tile<4, 1>(a, st);
+}
+
 }  // namespace
 
 int check_key_proj_supported(const KeyProjProblem &p, std::string *why)
@@ -346,6 +499,10 @@ int launch_key_proj(const KeyProjProblem &p, hipStream_t st, std::string *err)
     a.ovec = p.d % 8 == 0 && reinterpret_cast<uintptr_t>(p.O) % 16 == 0;
     a.kvec = p.d % 8 == 0 && p.r % 8 == 0 && reinterpret_cast<uintptr_t>(p.K) % 16 == 0;
     a.ncol = key_proj_col_tiles(p.d + p.r);
+    if (few_tiles(a) <= kFewTiles) {
+        launch_few(a, st);
+        return hip_status(hipGetLastError(), "key_proj_few launch", err);
+    }
     const int64_t tiles = (int64_t)a.ncol * ((p.N + kPM - 1) / kPM);
     hipLaunchKernelGGL(key_proj_gemm, dim3((unsigned)tiles), dim3(kPThreads), 0, st, a);
     return hip_status(hipGetLastError(), "key_proj_gemm launch", err);
