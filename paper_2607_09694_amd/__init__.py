@@ -145,10 +145,19 @@ def _dev(t, name, dtype=None):
     return t.data_ptr()
 
 
-def _stream(t):
-    import torch
+_raw_stream = None
 
-    return torch.cuda.current_stream(t.device).cuda_stream
+
+def _stream(t):
+    """The current stream of t's device, as its handle: torch's raw query
+    (0.1 us), or through a Stream object (1.9 us) where torch has none."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+    return _raw_stream(t.get_device())
 
 
 def _shape(V, K, q, mode):
