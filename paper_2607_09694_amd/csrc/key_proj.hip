@@ -71,6 +71,11 @@ struct ProjArgs {
     int64_t N;
     int m, d, r, ncol;
     bool ovec, kvec;    // O / K rows writable as 16-byte vectors
+    // The backward's dA = [dO, dK] W (SPLITK): A holds the first k0 columns of
+    // the reduction (rows of k0), A2 the other m - k0; W is the transposed
+    // weight, rows of sb elements.
+    const uint16_t *A2 = nullptr;
+    int k0 = 0, sb = 0;
 };
 
 // Column tiles: ncol - 1 of width 256, the last one the rest (<= 288).
@@ -86,7 +91,8 @@ __device__ __forceinline__ int chunk_at(int row, int c) { return row * kRow + 16
 
 // The k loop and epilogue of one workgroup; each wave computes NJ column
 // tiles of 16 (compile time, so that no MFMA sits behind a branch).
-template <int NJ>
+// SPLITK: the A operand in two tensors, split at column k0 (a multiple of kPK).
+template <int NJ, bool SPLITK = false>
 __device__ __forceinline__ void key_proj_tile(const ProjArgs &a, unsigned char *lds, int64_t n0,
                                               int j0, int width, int half)
 {
@@ -111,13 +117,36 @@ __device__ __forceinline__ void key_proj_tile(const ProjArgs &a, unsigned char *
     const int voff = rl * a.m * 2 + 16 * ((lane & 7) ^ ((rl >> 1) & 7));
     const int arows = (int)min((int64_t)kPM, a.N - n0);
     const int brows = max(0, min(width, nout - j0));
+    const int sa = SPLITK ? a.k0 : a.m, sw = SPLITK ? a.sb : a.m;  // row strides
     const __amdgpu_buffer_rsrc_t ares = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(a.A + n0 * a.m), 0, arows * a.m * 2, kRawBufferFlags);
+        (void *)(a.A + n0 * sa), 0, arows * sa * 2, kRawBufferFlags);
     const __amdgpu_buffer_rsrc_t bres = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(a.W + (size_t)j0 * a.m), 0, brows * a.m * 2, kRawBufferFlags);
+        (void *)(a.W + (size_t)j0 * sw), 0, brows * sw * 2, kRawBufferFlags);
     auto issue = [&](int kt, int buf) {
         unsigned char *sb = lds + buf * kStageBytes;
         const int kbytes = kt * kPK * 2;
+        if constexpr (SPLITK) {
+            // A from its first or its second tensor; each operand has its own
+            // row stride, so its own lane offset.
+            const bool first = kt * kPK < a.k0;
+            const int s2 = first ? a.k0 : a.m - a.k0;
+            const int swz = 16 * ((lane & 7) ^ ((rl >> 1) & 7));
+            const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)((first ? a.A : a.A2) + n0 * s2), 0, arows * s2 * 2, kRawBufferFlags);
+            const int kb = first ? kbytes : kbytes - a.k0 * 2;
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const int blk = wave + kWaves8 * u;
+                if (u < kABlocks / kWaves8)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void_t *)(sb + 1024 * blk), 16,
+                                                             rl * s2 * 2 + swz, u * 128 * s2 + kb, 0, 0);
+                else if (blk < kABlocks + kBBlocks)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        bres, (lds_void_t *)(sb + 1024 * blk), 16, rl * sw * 2 + swz,
+                        (u - kABlocks / kWaves8) * 128 * sw + kbytes, 0, 0);
+            }
+            return;
+        }
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
             const int blk = wave + kWaves8 * u;
@@ -277,6 +306,7 @@ __device__ __forceinline__ void key_proj_tile(const ProjArgs &a, unsigned char *
     }
 }
 
+template <bool SPLITK>
 __global__ __launch_bounds__(kPThreads, 1) void key_proj_gemm(ProjArgs a)
 {
     __shared__ __align__(16) unsigned char lds[2 * kStageBytes];
@@ -296,11 +326,11 @@ __global__ __launch_bounds__(kPThreads, 1) void key_proj_gemm(ProjArgs a)
     const int nct = (width + 15) / 16;
     const int half = (nct + 1) / 2;
     if (half <= 4)
-        key_proj_tile<4>(a, lds, n0, j0, width, half);
+        key_proj_tile<4, SPLITK>(a, lds, n0, j0, width, half);
     else if (half <= 8)
-        key_proj_tile<8>(a, lds, n0, j0, width, half);
+        key_proj_tile<8, SPLITK>(a, lds, n0, j0, width, half);
     else
-        key_proj_tile<9>(a, lds, n0, j0, width, half);
+        key_proj_tile<9, SPLITK>(a, lds, n0, j0, width, half);
 }
 
 // ---------------------------------------------------------------------------
@@ -420,6 +450,35 @@ __global__ __launch_bounds__(kFewThreads, 2) void key_proj_few(ProjArgs a)
     }
 }
 
+// Wt [m][sb] = W^T, zeros past the nout rows of W: 64 x 64 tiles through LDS,
+// 16 bytes a lane in and out.
+__global__ __launch_bounds__(256) void key_proj_transpose(const uint16_t *__restrict__ W,
+                                                          uint16_t *__restrict__ Wt, int nout,
+                                                          int m, int sb)
+{
+    __shared__ __align__(16) uint16_t tile[64][72];
+    const int o0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int f = threadIdx.x + 256 * u, row = f >> 3, c = 8 * (f & 7);
+        u32x4_t v = {0u, 0u, 0u, 0u};
+        if (o0 + row < nout && j0 + c < m)
+            v = load_raw<uint16_t, 8>(W + (size_t)(o0 + row) * m + j0 + c);
+        *reinterpret_cast<u32x4_t *>(&tile[row][c]) = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int f = threadIdx.x + 256 * u, row = f >> 3, c = 8 * (f & 7);
+        u32x4_t v;
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            v[h] = (unsigned)tile[c + 2 * h][row] | ((unsigned)tile[c + 2 * h + 1][row] << 16);
+        if (j0 + row < m)
+            store_raw<uint16_t, 8>(Wt + (size_t)(j0 + row) * sb + o0 + c, v);
+    }
+}
+
 template <int RT, int CT>
 void launch_few_tile(const ProjArgs &a, hipStream_t st)
 {
@@ -483,6 +542,53 @@ int check_key_proj_supported(const KeyProjProblem &p, std::string *why)
     return LRAR_OK;
 }
 
+// dA = [dO, dK] W with the forward's tiles, from a transposed copy of W: the
+// 256-wide tiles read half the LDS bytes per product of the backward's 128 x
+// 128 ones, which are bound by those reads.  One such workgroup fills a CU, so
+// the rule asks for one tile per CU and for rounds of 256 tiles that are
+// filled to 7/10.  Forward and backward at 1024 + 16 outputs, m = 2816, before
+// -> after: 704 tiles (16384 tokens) 398 -> 367 us, 506 tiles 304 -> 280, 374
+// tiles (filled to 0.73) 248 -> 246; outside it 297 tiles (0.58) 222 -> 228;
+// m = 1024, 128 tiles 101 -> 109.
+size_t key_proj_da_bytes(const KeyProjProblem &p)
+{
+    const int64_t tiles = (int64_t)key_proj_col_tiles(p.m) * ((p.N + kPM - 1) / kPM);
+    const int64_t rounds = (tiles + 255) / 256;
+    if (p.d == 0 || p.d % kPK != 0 || tiles < 256 || 10 * tiles < 7 * 256 * rounds)
+        return 0;
+    return (size_t)p.m * ((p.d + p.r + kPK - 1) / kPK * kPK) * sizeof(uint16_t);
+}
+
+hipError_t launch_key_proj_da(const KeyProjProblem &p, const void *dO, const void *dK, void *dA,
+                              void *wt, hipStream_t st)
+{
+    const int nout = (int)(p.d + p.r), sb = (nout + kPK - 1) / kPK * kPK;
+    uint16_t *Wt = static_cast<uint16_t *>(wt);
+    hipLaunchKernelGGL(key_proj_transpose, dim3(sb / 64, (unsigned)((p.m + 63) / 64)), dim3(256), 0,
+                       st, static_cast<const uint16_t *>(p.W), Wt, nout, (int)p.m, sb);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    ProjArgs a;
+    a.A = static_cast<const uint16_t *>(dO);
+    a.A2 = static_cast<const uint16_t *>(dK);
+    a.W = Wt;
+    a.O = static_cast<uint16_t *>(dA);
+    a.K = nullptr;
+    a.N = p.N;
+    a.m = nout;
+    a.d = (int)p.m;
+    a.r = 0;
+    a.k0 = (int)p.d;
+    a.sb = sb;
+    a.ovec = true;
+    a.kvec = false;
+    a.ncol = key_proj_col_tiles(p.m);
+    const int64_t tiles = (int64_t)a.ncol * ((p.N + kPM - 1) / kPM);
+    hipLaunchKernelGGL(key_proj_gemm<true>, dim3((unsigned)tiles), dim3(kPThreads), 0, st, a);
+    return hipGetLastError();
+}
+
 int launch_key_proj(const KeyProjProblem &p, hipStream_t st, std::string *err)
 {
     if (p.N == 0)
@@ -504,7 +610,7 @@ int launch_key_proj(const KeyProjProblem &p, hipStream_t st, std::string *err)
         return hip_status(hipGetLastError(), "key_proj_few launch", err);
     }
     const int64_t tiles = (int64_t)a.ncol * ((p.N + kPM - 1) / kPM);
-    hipLaunchKernelGGL(key_proj_gemm, dim3((unsigned)tiles), dim3(kPThreads), 0, st, a);
+    hipLaunchKernelGGL(key_proj_gemm<false>, dim3((unsigned)tiles), dim3(kPThreads), 0, st, a);
     return hip_status(hipGetLastError(), "key_proj_gemm launch", err);
 }
 

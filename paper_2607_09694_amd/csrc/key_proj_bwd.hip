@@ -26,6 +26,10 @@
 // are padded to 72 elements and rows of a transposed one to 144, which
 // spreads one operand read over the banks.
 //
+// These tiles are bound by their LDS reads; dA of many tokens therefore takes
+// the forward's larger ones, from a transposed copy of W in the workspace
+// (launch_key_proj_da).
+//
 // dA rounds to bf16 (nearest even).  dW is written in fp32, so that a caller
 // can add it to fp32 master gradients without a second rounding; its token
 // reduction is split over P workgroups per tile when the tile grid alone
@@ -357,10 +361,21 @@ int launch_key_proj_bwd(const KeyProjProblem &p, const void *dO, const void *dK,
     int64_t P;
     key_proj_bwd_splits(p.N, p.m, nout, &P, &a.per);
     if (p.N > 0) {
-        const int64_t tiles = ceil_div(p.N, kBM) * a.ntn;
-        hipLaunchKernelGGL(key_proj_bwd_gemm<false>, dim3((unsigned)tiles), dim3(kBThreads), 0,
-                           st, a);
-        int rc = hip_status(hipGetLastError(), "key_proj_bwd_gemm (dA) launch", err);
+        // dA with the forward's tiles from a transposed W, where the partials'
+        // workspace has room for that copy (the partials come after it).
+        const size_t da = key_proj_da_bytes(p);
+        hipError_t e;
+        if (da > 0 && da <= key_proj_bwd_workspace_bytes(p.N, p.m, p.d, p.r) &&
+            reinterpret_cast<uintptr_t>(workspace) % 16 == 0 &&
+            reinterpret_cast<uintptr_t>(dA) % 16 == 0) {
+            e = launch_key_proj_da(p, dO, dK, dA, workspace, st);
+        } else {
+            const int64_t tiles = ceil_div(p.N, kBM) * a.ntn;
+            hipLaunchKernelGGL(key_proj_bwd_gemm<false>, dim3((unsigned)tiles), dim3(kBThreads), 0,
+                               st, a);
+            e = hipGetLastError();
+        }
+        int rc = hip_status(e, "key_proj_bwd (dA) launch", err);
         if (rc)
             return rc;
         a.dst = P > 1 ? static_cast<float *>(workspace) : dW;

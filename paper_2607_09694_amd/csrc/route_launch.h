@@ -212,6 +212,11 @@ int launch_key_proj(const KeyProjProblem &p, hipStream_t st, std::string *err);
 // workspace holds the token splits' partials (key_proj_bwd_workspace_bytes).
 void key_proj_bwd_splits(int64_t N, int64_t m, int64_t nout, int64_t *P, int64_t *per);
 size_t key_proj_bwd_workspace_bytes(int64_t N, int64_t m, int64_t d, int64_t r);
+// dA with the forward's tiles: the workspace it needs, or 0 where it does not
+// apply, and the launch (wt: that many bytes, 16-byte aligned).
+size_t key_proj_da_bytes(const KeyProjProblem &p);
+hipError_t launch_key_proj_da(const KeyProjProblem &p, const void *dO, const void *dK, void *dA,
+                              void *wt, hipStream_t st);
 int check_key_proj_bwd_supported(const KeyProjProblem &p, std::string *why);
 int launch_key_proj_bwd(const KeyProjProblem &p, const void *dO, const void *dK, void *dA,
                         float *dW, void *workspace, hipStream_t st, std::string *err);
