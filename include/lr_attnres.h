@@ -87,7 +87,8 @@ int lr_attnres_route_fwd(const void *V, const void *K, const float *q, void *H,
 
 /*
  * Bytes of device workspace lr_attnres_route_bwd needs for this problem
- * (per-workgroup partial sums of dq).  0 for an invalid problem.
+ * (per-workgroup partial sums of dq; for full-rank keys in bf16 the softmax
+ * gradients of every token, where that is more).  0 for an invalid problem.
  */
 size_t lr_attnres_route_bwd_workspace_bytes(int64_t S, int64_t N, int64_t d, int64_t r,
                                             int mode, int dtype);
@@ -146,7 +147,7 @@ int lr_attnres_route_bwd_accumulate(const void *V, const void *K, const float *q
  *   Arguments, results, validation and errors are those of
  *   lr_attnres_route_bwd with the workspace removed, plus LRAR_EUNSUPPORTED
  *   when the problem needs more than 8 MiB of partials
- *   (lr_attnres_route_bwd_workspace_bytes > 8388608: e.g. r = 32 beyond
+ *   (the form that uses a larger workspace is not taken then; e.g. r = 32 beyond
  *   2^19 tokens with projected keys, or full rank at d = 1024 beyond
  *   32768 tokens).
  *   All calls on one device share the array, and each call leaves its

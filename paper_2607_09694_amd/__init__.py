@@ -265,7 +265,7 @@ def route_all_fwd(V, K, Q, mode, first: int, eps: float = 1e-6, with_neff: bool 
     V [S,N,d] bf16/fp32; K [S,N,r] (projected) or None (sliced, full-rank);
     Q [T,r] fp32 (full-rank: r = d).  Returns (H [T,N,d] in V's dtype, neff
     [T,N] fp32 or None), neff per Eq. effective_sources.  ``out`` may supply
-    (H, neff).  Problems outside the fused kernel run site by site inside
+    (H, neff).  Problems outside the fused kernels run site by site inside
     the library.
     """
     import torch

@@ -56,10 +56,9 @@ struct AllArgs {
 // bf16 storage can take the keys already loaded (kpre, from load_site_keys,
 // so that they can be issued ahead of other loads) and the queries from LDS
 // (qlds, Q [T][r]); by default both are read here from global memory.
-// Sum and maximum over the 16 lanes of each row of the wave, returned to
-// all 16: four DPP moves (group_sum / group_max over groups of 16).
+// Sum over the 16 lanes of each row of the wave, returned to all 16: four DPP
+// moves (group_sum over groups of 16).
 __device__ __forceinline__ float row16_sum(float x) { return group_sum(x, 16); }
-__device__ __forceinline__ float row16_max(float x) { return group_max(x, 16); }
 
 // Whether site `site` reads source i.
 __device__ __forceinline__ bool read_by(const AllArgs &a, int site, int i)
@@ -305,7 +304,7 @@ __device__ __forceinline__ void all_site_weights(const AllArgs &a, int64_t n, fl
 }
 
 // ---------------------------------------------------------------------------
-// Sliced keys wider than kAllMaxRank columns, bf16 storage.
+// Keys wider than kAllMaxRank columns (sliced or full rank), bf16 storage.
 // ---------------------------------------------------------------------------
 
 // 8 fp32 values as three bf16 operands whose sum is exact to fp32's 24 bits

@@ -55,21 +55,6 @@ struct WideBwdArgs {
     float *cq;           // [N][T][64] ds / rho
 };
 
-// 8 rows of 8 consecutive columns (one 16-byte row per register quad) as 8
-// operands that hold one column of the 8 rows.
-__device__ __forceinline__ void transpose8(const u32x4_t (&w)[8], bf16x8_t (&b)[8])
-{
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        u32x4_t q;
-#pragma unroll
-        for (int h = 0; h < 4; ++h)
-            q[h] = (p & 1) ? hi_pair(w[2 * h][p / 2], w[2 * h + 1][p / 2])
-                           : lo_pair(w[2 * h][p / 2], w[2 * h + 1][p / 2]);
-        b[p] = __builtin_bit_cast(bf16x8_t, q);
-    }
-}
-
 // 8 fp32 values as hi + lo bf16 (relative 2^-17).
 __device__ __forceinline__ void split2(const float (&v)[8], bf16x8_t &hi, bf16x8_t &lo)
 {

@@ -471,39 +471,6 @@ __device__ __forceinline__ void mix_batch_fma(const typename Raw<T, VEC>::type (
     }
 }
 
-template <typename T, int VEC, int NCH, bool FULLCOLS, int U>
-__device__ __forceinline__ void mix_rows_pipelined(typename Raw<T, VEC>::type (&ra)[U][NCH],
-                                                   const T *__restrict__ vbase, size_t plane,
-                                                   int S, const float *alpha,
-                                                   const bool (&ok)[NCH], float (&acc)[NCH][VEC])
-{
-    typename Raw<T, VEC>::type rb[U][NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-#pragma unroll
-        for (int e = 0; e < VEC; ++e)
-            acc[c][e] = 0.0f;
-    // ra holds batch 0 (sources 0 .. U-1) on entry; nb batches in all.
-    const int nb = (S + U - 1) / U;
-    int b = 0;
-    for (; b + 2 < nb; b += 2) {
-        mix_batch_load<T, VEC, NCH, FULLCOLS, U>(rb, vbase, plane, (b + 1) * U, S, ok);
-        __builtin_amdgcn_sched_barrier(0);
-        mix_batch_fma<T, VEC, NCH, FULLCOLS, U>(ra, alpha, b * U, S, ok, acc);
-        mix_batch_load<T, VEC, NCH, FULLCOLS, U>(ra, vbase, plane, (b + 2) * U, S, ok);
-        __builtin_amdgcn_sched_barrier(0);
-        mix_batch_fma<T, VEC, NCH, FULLCOLS, U>(rb, alpha, (b + 1) * U, S, ok, acc);
-    }
-    if (b + 1 < nb) {
-        mix_batch_load<T, VEC, NCH, FULLCOLS, U>(rb, vbase, plane, (b + 1) * U, S, ok);
-        __builtin_amdgcn_sched_barrier(0);
-        mix_batch_fma<T, VEC, NCH, FULLCOLS, U>(ra, alpha, b * U, S, ok, acc);
-        mix_batch_fma<T, VEC, NCH, FULLCOLS, U>(rb, alpha, (b + 1) * U, S, ok, acc);
-    } else {
-        mix_batch_fma<T, VEC, NCH, FULLCOLS, U>(ra, alpha, b * U, S, ok, acc);
-    }
-}
-
 template <typename T, int VEC, int NCH, bool FULLCOLS>
 __device__ __forceinline__ void store_row(T *__restrict__ base, const bool (&ok)[NCH],
                                           const float (&acc)[NCH][VEC])

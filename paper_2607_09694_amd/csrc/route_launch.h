@@ -169,7 +169,7 @@ int check_all_supported(const AllProblem &p, std::string *why);
 // keys, S, T, r <= 64, d % 8 == 0); otherwise the sites run one by one.
 bool all_fused(const AllProblem &p);
 // Whether the fused kernels of wide keys take it (bf16 storage, sliced keys
-// of more than 64 columns, S and T <= 64, 16-byte key rows).
+// of more than 64 columns or full-rank keys, S and T <= 64, 16-byte key rows).
 bool all_wide(const AllProblem &p);
 // Their backward; the workspace is 4-byte aligned, dK does not exist.
 size_t wide_bwd_workspace_bytes(int64_t N, int64_t T, int64_t r);
