@@ -153,7 +153,9 @@ route_bwd_full(const T *__restrict__ V, const float *__restrict__ q, const T *__
 
 // dq[j] = sum_b partial[b][j] in a fixed order: one workgroup per column;
 // thread t sums rows t, t+256, ... in order, then a fixed pairwise tree over
-// the 256 thread sums.  Writes zeros when nblocks = 0.
+// the 256 thread sums.  Writes zeros when nblocks = 0.  Bound by latency: four
+// rows' loads are in flight together, and the tree's last six steps are one
+// wave's lane exchanges.
 template <bool ACC>
 __global__ void __launch_bounds__(256)
 dq_reduce(const float *__restrict__ partial, float *__restrict__ dq, int nblocks, int ncols)
@@ -162,18 +164,25 @@ dq_reduce(const float *__restrict__ partial, float *__restrict__ dq, int nblocks
     const int t = threadIdx.x;
     const int j = blockIdx.x;
     float s = 0.0f;
-    for (int b = t; b < nblocks; b += 256)
-        s += partial[(size_t)b * ncols + j];
-    red[t] = s;
-    __syncthreads();
+    for (int b = t; b < nblocks; b += 1024) {
+        float v[4];
 #pragma unroll
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (t < w)
-            red[t] += red[t + w];
-        __syncthreads();
+        for (int u = 0; u < 4; ++u)
+            v[u] = partial[(size_t)min(b + 256 * u, nblocks - 1) * ncols + j];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            s += b + 256 * u < nblocks ? v[u] : 0.0f;
     }
+    red[t] = s;
+    lds_barrier();
+    if (t >= 64)
+        return;
+    s = (red[t] + red[t + 128]) + (red[t + 64] + red[t + 192]);
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1)
+        s += __shfl_down(s, w, kWaveSize);
     if (t == 0)
-        dq[j] = ACC ? dq[j] + red[0] : red[0];
+        dq[j] = ACC ? dq[j] + s : s;
 }
 
 hipError_t launch_dq_reduce(const float *partial, float *dq, int nblocks, int ncols,
