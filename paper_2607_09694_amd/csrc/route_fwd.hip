@@ -15,16 +15,17 @@ namespace lrar {
 // each token's softmax into its own LDS slice, and streams the sources in
 // batches of SB, each batch loading the SB sources' rows of all TW tokens
 // (adjacent in each source plane) before accumulating them.  Tokens past N
-// re-read row N-1 and are not stored; sources past S re-read source S-1
+// re-read row N-1 and are not stored (ONE: one token per wave, two sources a
+// batch instead; the sums keep their order); sources past S re-read source S-1
 // (the same lines, in flight together) and are not accumulated.
-template <typename T, int VEC, int NCH, bool FULLCOLS>
+template <typename T, int VEC, int NCH, bool FULLCOLS, bool ONE>
 __global__ void __launch_bounds__(kBlock)
 route_fwd_lr(const T *__restrict__ V, const T *__restrict__ keys, const float *__restrict__ q,
              T *__restrict__ H, int S, int N, int d, int r, int krow, int koff, float eps,
              int s_pad)
 {
-    constexpr int TW = fwd_tokens_per_wave(NCH);
-    constexpr int SB = fwd_sources_per_batch(NCH);
+    constexpr int TW = ONE ? 1 : fwd_tokens_per_wave(NCH);
+    constexpr int SB = !ONE ? fwd_sources_per_batch(NCH) : NCH <= 2 ? 2 : 1;
     typedef typename Raw<T, VEC>::type raw_t;
     extern __shared__ float lds[];
     const int lane = threadIdx.x & (kWaveSize - 1);
@@ -552,6 +553,15 @@ route_fwd_full_1p(const T *__restrict__ V, const float *__restrict__ q, T *__res
 
 namespace {
 
+// Tokens up to which a wave of route_fwd_lr takes one token: two a wave leave
+// half of the waves of a round (256 CUs, 16 waves each) without work there,
+// and the rest have too few loads in flight.  Two tokens -> one: sliced r =
+// 64, 33 sources, d = 1024: 2100 tokens 50 -> 32 us, 4099 tokens 57 -> 47 us
+// (5.0 -> 6.0 TB/s), 5600 tokens 65 -> 66; projected r = 16, 49 sources: d =
+// 2048, 3000 tokens 134 -> 89, 4096 tokens 144 -> 123; d = 1024, 4608 tokens
+// 79 -> 78, 5120 tokens 81 -> 83; fp32, 33 sources, 4500 tokens 99 -> 100.
+constexpr int64_t kOneTokenFwd = 4352;
+
 template <typename T, int VEC>
 hipError_t launch_fwd_t(const Problem &p, const Plan &pl, void *H, hipStream_t st)
 {
@@ -577,12 +587,19 @@ hipError_t launch_fwd_t(const Problem &p, const Plan &pl, void *H, hipStream_t s
                                (int)p.S, (int)p.N, (int)p.d, (int)p.r, krow, koff, p.eps,
                                pl.s_pad);
         } else {
-            constexpr int TW = fwd_tokens_per_wave(NCH);
-            const int nb = (int)((p.N + kWaves * TW - 1) / (kWaves * TW));
-            hipLaunchKernelGGL((route_fwd_lr<T, VEC, NCH, FC>), dim3(nb, pl.ysplit),
-                               dim3(kBlock), pl.lds * TW, st, V, keys, p.q, static_cast<T *>(H),
-                               (int)p.S, (int)p.N, (int)p.d, (int)p.r, krow, koff, p.eps,
-                               pl.s_pad);
+            auto launch = [&](auto one) {
+                constexpr bool ONE = decltype(one)::value;
+                constexpr int TW = ONE ? 1 : fwd_tokens_per_wave(NCH);
+                const int nb = (int)((p.N + kWaves * TW - 1) / (kWaves * TW));
+                hipLaunchKernelGGL((route_fwd_lr<T, VEC, NCH, FC, ONE>), dim3(nb, pl.ysplit),
+                                   dim3(kBlock), pl.lds * TW, st, V, keys, p.q,
+                                   static_cast<T *>(H), (int)p.S, (int)p.N, (int)p.d, (int)p.r,
+                                   krow, koff, p.eps, pl.s_pad);
+            };
+            if (fwd_tokens_per_wave(NCH) > 1 && p.N <= kOneTokenFwd)
+                launch(std::bool_constant<fwd_tokens_per_wave(NCH) != 1>{});
+            else
+                launch(std::false_type{});
         }
         return hipGetLastError();
     });
