@@ -20,6 +20,19 @@ constexpr int kAllSlab = 128;                     // columns per wave pass
 constexpr int kAlphaRow = kAllMaxSources + 4;     // floats per LDS alpha row
 constexpr int kKeyRow = kAllMaxRank + 8;          // bf16 per LDS key row
 
+// 8 fp32 values as hi + lo bf16 (relative 2^-17).
+__device__ __forceinline__ void split2(const float (&v)[8], bf16x8_t &hi, bf16x8_t &lo)
+{
+    u32x4_t h, l;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        h[k] = pack_bf16x2(v[2 * k], v[2 * k + 1]);
+        l[k] = pack_bf16x2(v[2 * k] - bf16_lo(h[k]), v[2 * k + 1] - bf16_hi(h[k]));
+    }
+    hi = __builtin_bit_cast(bf16x8_t, h);
+    lo = __builtin_bit_cast(bf16x8_t, l);
+}
+
 struct AllArgs {
     const void *V;       // [S][N][d]
     const void *keys;    // projected: K [S][N][r]; sliced: V

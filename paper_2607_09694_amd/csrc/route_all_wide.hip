@@ -55,19 +55,6 @@ struct WideBwdArgs {
     float *cq;           // [N][T][64] ds / rho
 };
 
-// 8 fp32 values as hi + lo bf16 (relative 2^-17).
-__device__ __forceinline__ void split2(const float (&v)[8], bf16x8_t &hi, bf16x8_t &lo)
-{
-    u32x4_t h, l;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        h[k] = pack_bf16x2(v[2 * k], v[2 * k + 1]);
-        l[k] = pack_bf16x2(v[2 * k] - bf16_lo(h[k]), v[2 * k + 1] - bf16_hi(h[k]));
-    }
-    hi = __builtin_bit_cast(bf16x8_t, h);
-    lo = __builtin_bit_cast(bf16x8_t, l);
-}
-
 // One slab of dV (or its key term) summed over the reading sites only, on the
 // vector units: taken when the matrix form gave a non-finite value, since an
 // infinite or NaN upstream value of a site that doesn't read a source enters

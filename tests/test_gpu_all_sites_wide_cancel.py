@@ -1,0 +1,66 @@
+"""Cancelling sums of the all-sites calls with sliced keys wider than 64
+columns: the routed states as exact as weights in fp32 make them.
+
+Sources whose weighted values cancel to 2^-18 of their terms leave nothing of
+the bf16 rounding of H, so what shows is the error of the weights alone: fp32
+softmax weights of a few sources with scores around 1 carry about ten
+roundings (score, norm, exponential, sum, quotient), and the sum over the
+sources one per term at most.  Bar per entry: (16 + S) 2^-24 sum |alpha v| +
+2^-8 |H|, the latter bf16's half-ulp.  Weights in two bf16 terms (2^-18 each
+at most) miss it nearly threefold at 8 sources; what is measured is 0.2 of it.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2607_09694_amd as lr
+from paper_2607_09694_amd.inputs import SLICED, bf16_bits_from_f32, f32_from_bf16_bits
+from test_gpu_all_sites_bwd import dev, to_dev, to_host  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+U = 2.0 ** -24
+
+
+def bf16(x):
+    return f32_from_bf16_bits(bf16_bits_from_f32(np.asarray(x, dtype=np.float32))).astype(np.float64)
+
+
+def weights(V, Q, first, r):
+    """fp64 weights [T, S, N], zero past each site's prefix."""
+    T, (S, N, _) = Q.shape[0], V.shape
+    a = np.zeros((T, S, N))
+    for j in range(T):
+        a[j, :first + j] = oracle.route_weights(V[:first + j], None, Q[j].astype(np.float64), SLICED,
+                                                r=r).T
+    return a
+
+
+# (S, T, first, N, d, r): one to four site tiles
+CASES = [(8, 7, 2, 40, 328, 72), (12, 11, 2, 9, 1000, 256), (33, 32, 2, 5, 520, 128),
+         (49, 48, 2, 3, 328, 72), (64, 64, 1, 3, 200, 72)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "S{}-T{}-f{}-N{}-d{}-r{}".format(*c))
+def test_cancelling_states_keep_fp32_weights(dev, case):  # noqa: F811
+    S, T, first, N, d, r = case
+    rng = np.random.default_rng(S + N + d)
+    V = bf16(rng.standard_normal((S, N, d)))
+    # scores of about 1: |kbar| = sqrt(r)
+    Q = (rng.standard_normal((T, r)) / np.sqrt(r)).astype(np.float32)
+    a = weights(bf16_bits_from_f32(V.astype(np.float32)), Q, first, r)
+    # the last two sources cancel the last site's sum in the value columns
+    for i in (S - 2, S - 1):
+        rest = (a[T - 1, :, :, None] * V)[:i].sum(0)
+        V[i, :, :d - r] = bf16(-rest[:, :d - r] / a[T - 1, i][:, None])[:, :d - r]
+    Vb = bf16_bits_from_f32(V.astype(np.float32))
+    ref = np.einsum("jin,inc->jnc", a, V)[..., :d - r]
+    mag = np.einsum("jin,inc->jnc", a, np.abs(V))[..., :d - r]
+    assert np.median(np.abs(ref[-1]) / mag[-1]) < 2.0 ** -16
+    H, _ = lr.route_all_fwd(to_dev(Vb, dev), None, to_dev(Q, dev), SLICED, first)
+    torch.cuda.synchronize()
+    err = np.abs(to_host(H)[..., :d - r].astype(np.float64) - ref)
+    # sites whose sums do not cancel are bound by the bf16 rounding of H
+    worst = (err / ((16 + S) * U * mag + 2.0 ** -8 * np.abs(ref))).max(axis=(1, 2))
+    assert worst.max() <= 1.0, f"error / bar by site: {worst}"
