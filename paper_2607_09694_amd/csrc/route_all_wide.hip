@@ -9,13 +9,16 @@
 //   route_all_bwd_wide (one token per workgroup, 4 waves)
 //     1. the waves contract whole rows on the matrix cores (wide_products):
 //        D = Q K^T and G = dH V^T from one read of the rows; wave w then
-//        holds the sites of tile w; softmax and softmax gradient in registers; alpha and cq = ds / rho to LDS as hi + lo bf16,
-//        [source][site], and cq to the workspace in fp32;
+//        holds the sites of tile w; softmax and softmax gradient in registers;
+//        alpha and cq = ds / rho to LDS as three bf16 terms each (all of fp32's
+//        24 bits), [source][site], and cq to the workspace in fp32;
 //     2. each wave takes 64-column slabs of all 64 sources:
 //            dV = alpha^T dH + (key columns) cq^T Q - ck k
 //        with the upstream rows transposed in registers as in the forward
-//        and Q as hi + lo (three MFMAs), ck_i = sum_j ds s / (rho_i^2 r).
-//   wide_dq (one 128-column slab of the keys and one share of the tokens per
+//        and Q as three terms (the six products of cq Q down to 2^-24: 5 us of
+//        299 at r = 256 as below, 30 of 451 at full rank, against two terms),
+//        ck_i = sum_j ds s / (rho_i^2 r).
+//   wide_dq (one 64-column slab of the keys and one share of the tokens per
 //     wave): dQ += cq K over its tokens in registers, on the fp32 matrix
 //     cores, then a fixed-order sum of the shares.
 //
@@ -46,6 +49,7 @@ constexpr int kDqAhead = 3;                 // source groups in flight in the dQ
 constexpr int kDqOneSlab = 256;             // columns per workgroup of the one-site dQ product
 constexpr int kWideSlab = 64;               // columns per wave pass of the value gradient
 constexpr int kOpRow = kAllMaxSources + 8;  // bf16 per LDS row of an operand [source][site]
+constexpr int kOp = kAllMaxSources * kOpRow;
 
 struct WideBwdArgs {
     AllArgs f;           // V, Q, sizes; f.S: sources that some site reads
@@ -62,8 +66,7 @@ struct WideBwdArgs {
 // every tile.
 template <bool ACC>
 __device__ __forceinline__ void wide_dv_prefixes(const WideBwdArgs &b, int64_t n,
-                                              const uint16_t *ahi, const uint16_t *alo,
-                                              const float *ck, int c0, int ks)
+                                              const uint16_t *at, const float *ck, int c0, int ks)
 {
     const AllArgs &a = b.f;
     if (c0 >= a.d)
@@ -77,7 +80,8 @@ __device__ __forceinline__ void wide_dv_prefixes(const WideBwdArgs &b, int64_t n
         float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 1
         for (int j = max(0, i + 1 - a.first); j < a.T && i < a.S; ++j) {
-            const float w = load_elem(ahi + i * kOpRow + j) + load_elem(alo + i * kOpRow + j);
+            const uint16_t *o = at + i * kOpRow + j;
+            const float w = load_elem(o) + (load_elem(o + kOp) + load_elem(o + 2 * kOp));
             float x[4];
             widen(load_raw<uint16_t, 4>(b.dH + j * plane + n * a.d + c0), x);
             const float cq = b.cq[((size_t)n * a.T + j) * kAllMaxSources + i];
@@ -103,16 +107,23 @@ __device__ __forceinline__ void wide_dv_prefixes(const WideBwdArgs &b, int64_t n
     }
 }
 
+// The next bf16 term of four values (nearest even), taken off them.
+__device__ __forceinline__ u32x2_t next_term(f32x4_t &v)
+{
+    const u32x2_t w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+    v -= f32x4_t{bf16_lo(w[0]), bf16_hi(w[0]), bf16_lo(w[1]), bf16_hi(w[1])};
+    return w;
+}
+
 template <int MT, bool ACC>
 __global__ __launch_bounds__(kBlock, 2) void route_all_bwd_wide(WideBwdArgs b)
 {
     constexpr int KG = (MT + 1) / 2;  // groups of 32 sites in the contractions over sites
     // The exchange of the products, then the operands of the value gradient.
-    constexpr int kOp = kAllMaxSources * kOpRow;
     __shared__ __align__(16)
-        unsigned char lds[std::max<int>(wide_exchange_bytes<MT>(), 4 * kOp * sizeof(uint16_t))];
-    uint16_t *const ahi = reinterpret_cast<uint16_t *>(lds), *const alo = ahi + kOp;
-    uint16_t *const chi = alo + kOp, *const clo = chi + kOp;
+        unsigned char lds[std::max<int>(wide_exchange_bytes<MT>(), 6 * kOp * sizeof(uint16_t))];
+    // alpha and cq in three bf16 terms each, the largest first.
+    uint16_t *const at = reinterpret_cast<uint16_t *>(lds), *const ct = at + 3 * kOp;
     __shared__ float rho[kAllMaxSources], ck[kAllMaxSources], part[kWaves * kAllMaxSources];
     const AllArgs &a = b.f;
     const int64_t n = xcd_block().x;  // each XCD a range of tokens (up to 8% faster)
@@ -129,23 +140,15 @@ __global__ __launch_bounds__(kBlock, 2) void route_all_bwd_wide(WideBwdArgs b)
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
             const int i = 16 * nt + lc;
-            // Four consecutive sites of source i: one 8-byte write per array.
-            u32x2_t h, l;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                h[k] = pack_bf16x2(al[nt][2 * k], al[nt][2 * k + 1]);
-                l[k] = pack_bf16x2(al[nt][2 * k] - bf16_lo(h[k]), al[nt][2 * k + 1] - bf16_hi(h[k]));
-            }
+            // Four consecutive sites of source i: one 8-byte write per term.
             const int o = i * kOpRow + 16 * wave + 4 * ks;
-            *reinterpret_cast<u32x2_t *>(ahi + o) = h;
-            *reinterpret_cast<u32x2_t *>(alo + o) = l;
+            f32x4_t x = {al[nt][0], al[nt][1], al[nt][2], al[nt][3]};
+            f32x4_t y = {cq[nt][0], cq[nt][1], cq[nt][2], cq[nt][3]};
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                h[k] = pack_bf16x2(cq[nt][2 * k], cq[nt][2 * k + 1]);
-                l[k] = pack_bf16x2(cq[nt][2 * k] - bf16_lo(h[k]), cq[nt][2 * k + 1] - bf16_hi(h[k]));
+            for (int t = 0; t < 3; ++t) {
+                *reinterpret_cast<u32x2_t *>(at + t * kOp + o) = next_term(x);
+                *reinterpret_cast<u32x2_t *>(ct + t * kOp + o) = next_term(y);
             }
-            *reinterpret_cast<u32x2_t *>(chi + o) = h;
-            *reinterpret_cast<u32x2_t *>(clo + o) = l;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int site = 16 * wave + 4 * ks + e;
@@ -213,7 +216,7 @@ __global__ __launch_bounds__(kBlock, 2) void route_all_bwd_wide(WideBwdArgs b)
 #pragma unroll
             for (int kg = 0; kg < KG; ++kg) {
                 // Operands: one column of the lane's 8 sites each.
-                bf16x8_t B[4], Qh[4], Ql[4];
+                bf16x8_t B[4], Q[3][4];
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
                     u32x4_t x;
@@ -230,7 +233,7 @@ __global__ __launch_bounds__(kBlock, 2) void route_all_bwd_wide(WideBwdArgs b)
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
                             v[e] = kok ? q[e][p] : 0.0f;
-                        split2(v, Qh[p], Ql[p]);
+                        split3(v, Q[0][p], Q[1][p], Q[2][p]);
                     }
                 }
                 // The next group, or the next slab's first (the last slab's
@@ -243,26 +246,24 @@ __global__ __launch_bounds__(kBlock, 2) void route_all_bwd_wide(WideBwdArgs b)
                     if (16 * nt >= a.S)
                         continue;  // wave-uniform
                     const int o = (16 * nt + lc) * kOpRow + 32 * kg + 8 * ks;
-                    const bf16x8_t Ah = *reinterpret_cast<const bf16x8_t *>(ahi + o);
-                    const bf16x8_t Al = *reinterpret_cast<const bf16x8_t *>(alo + o);
+                    // Smallest terms first; of cq Q the products down to 2^-24.
 #pragma unroll
-                    for (int p = 0; p < 4; ++p)
-                        acc[nt][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Al, B[p], acc[nt][p], 0, 0, 0);
+                    for (int t = 2; t >= 0; --t) {
+                        const bf16x8_t A = *reinterpret_cast<const bf16x8_t *>(at + t * kOp + o);
 #pragma unroll
-                    for (int p = 0; p < 4; ++p)
-                        acc[nt][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah, B[p], acc[nt][p], 0, 0, 0);
+                        for (int p = 0; p < 4; ++p)
+                            acc[nt][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B[p], acc[nt][p], 0, 0, 0);
+                    }
                     if (KEY) {
-                        const bf16x8_t Ch = *reinterpret_cast<const bf16x8_t *>(chi + o);
-                        const bf16x8_t Cl = *reinterpret_cast<const bf16x8_t *>(clo + o);
 #pragma unroll
-                        for (int p = 0; p < 4; ++p)
-                            acc[nt][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Cl, Qh[p], acc[nt][p], 0, 0, 0);
+                        for (int t = 2; t >= 0; --t) {
+                            const bf16x8_t C = *reinterpret_cast<const bf16x8_t *>(ct + t * kOp + o);
 #pragma unroll
-                        for (int p = 0; p < 4; ++p)
-                            acc[nt][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ch, Ql[p], acc[nt][p], 0, 0, 0);
+                            for (int u = 2 - t; u >= 0; --u)
 #pragma unroll
-                        for (int p = 0; p < 4; ++p)
-                            acc[nt][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ch, Qh[p], acc[nt][p], 0, 0, 0);
+                                for (int p = 0; p < 4; ++p)
+                                    acc[nt][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(C, Q[u][p], acc[nt][p], 0, 0, 0);
+                        }
                     }
                 }
             }
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(kBlock, 2) void route_all_bwd_wide(WideBwdArgs b)
                     for (int e = 0; e < 4; ++e)
                         bad = fmaf(acc[nt][p][e], 0.0f, bad);
             if (__any(bad != 0.0f)) {
-                wide_dv_prefixes<ACC>(b, n, ahi, alo, ck, c0, ks);
+                wide_dv_prefixes<ACC>(b, n, at, ck, c0, ks);
                 continue;
             }
             u32x2_t vk[4][4];

@@ -1,5 +1,6 @@
 """Cancelling sums of the all-sites calls with sliced keys wider than 64
-columns: the routed states as exact as weights in fp32 make them.
+columns: the routed states and the value gradients as exact as weights in fp32
+make them.
 
 Sources whose weighted values cancel to 2^-18 of their terms leave nothing of
 the bf16 rounding of H, so what shows is the error of the weights alone: fp32
@@ -8,6 +9,8 @@ roundings (score, norm, exponential, sum, quotient), and the sum over the
 sources one per term at most.  Bar per entry: (16 + S) 2^-24 sum |alpha v| +
 2^-8 |H|, the latter bf16's half-ulp.  Weights in two bf16 terms (2^-18 each
 at most) miss it nearly threefold at 8 sources; what is measured is 0.2 of it.
+The value gradient sums weights times upstream rows over the sites, T terms,
+and is held to the same bar.
 """
 import numpy as np
 import pytest
@@ -64,3 +67,28 @@ def test_cancelling_states_keep_fp32_weights(dev, case):  # noqa: F811
     # sites whose sums do not cancel are bound by the bf16 rounding of H
     worst = (err / ((16 + S) * U * mag + 2.0 ** -8 * np.abs(ref))).max(axis=(1, 2))
     assert worst.max() <= 1.0, f"error / bar by site: {worst}"
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "S{}-T{}-f{}-N{}-d{}-r{}".format(*c))
+@pytest.mark.parametrize("accumulate", [False, True], ids=["write", "add"])
+def test_cancelling_value_gradients_keep_fp32_weights(dev, case, accumulate):  # noqa: F811
+    """The last two sites' upstream rows cancel source 0's sum over the sites."""
+    S, T, first, N, d, r = case
+    rng = np.random.default_rng(S * N + d)
+    Vb = bf16_bits_from_f32(rng.standard_normal((S, N, d)).astype(np.float32))
+    Q = (rng.standard_normal((T, r)) / np.sqrt(r)).astype(np.float32)
+    a = weights(Vb, Q, first, r)
+    dH = bf16(rng.standard_normal((T, N, d)))
+    for j in (T - 2, T - 1):
+        dH[j] = bf16(-(a[:, 0, :, None] * dH)[:j].sum(0) / a[j, 0][:, None])
+    ref = np.einsum("jin,jnc->inc", a, dH)[..., :d - r]
+    mag = np.einsum("jin,jnc->inc", a, np.abs(dH))[..., :d - r]
+    assert np.median(np.abs(ref[0]) / mag[0]) < 2.0 ** -16
+    dHd = to_dev(bf16_bits_from_f32(dH.astype(np.float32)), dev)
+    V, Qd = to_dev(Vb, dev), to_dev(Q, dev)
+    out = (torch.zeros_like(V), None, torch.zeros_like(Qd)) if accumulate else None
+    dV, _, _ = lr.route_all_bwd(V, None, Qd, dHd, SLICED, first, out=out, accumulate=accumulate)
+    torch.cuda.synchronize()
+    err = np.abs(to_host(dV)[..., :d - r].astype(np.float64) - ref)
+    worst = (err / ((16 + T) * U * mag + 2.0 ** -8 * np.abs(ref))).max(axis=(1, 2))
+    assert worst.max() <= 1.0, f"error / bar by source: {worst}"
