@@ -571,16 +571,18 @@ __global__ __launch_bounds__(kBlock, 2) void route_bwd_full_rows(WideBwdArgs b)
 
 // dQ shares.  Wave `id` of the grid's y dimension sums
 //     share[j][c] = sum_n sum_i cq[n][j][i] k[n][i][c]
-// over its tokens n = id, id + waves, ... in order (each token's sum on its
-// own, then the tokens': two short chains of fp32 additions instead of one of
-// thousands), for the 64 key columns of slab blockIdx.x, on the fp32 matrix cores: a lane's 8-byte row pieces,
+// over its tokens n = id, id + waves, ... in order, for the 64 key columns of
+// slab blockIdx.x, on the fp32 matrix cores: a lane's 8-byte row pieces,
 // widened, are the operands as they stand (16 sources a group, four a step,
 // lane group ks taking sources 4 ks .. 4 ks + 3 of the group, so that its cq
-// come as one 16-byte vector).  The bf16 matrix cores with cq as three terms
-// took 27 us against 44 (49 sources, 48 sites, r = 256, 2048 tokens), but
-// round long sums coarsely: the error of dQ grew with the tokens, from 1.8e-7
-// to 3.4e-7 at 2048 (site by site 2.1e-7); these stay below the single-site
-// kernels' errors at every number of tokens.  The 4 waves of a workgroup then add up in wave order.
+// come as one 16-byte vector).  The sum of a group starts from zero, a token's
+// groups add up on their own, then the tokens, then the 4 waves of a workgroup:
+// short chains of fp32 additions, so that dQ is 0.76 - 0.96 times as far from
+// 64 bits as the site-by-site calls (1 to 7000 tokens, 5 to 64 sources; up to
+// 1.06 times with one chain over a token and the shares summed in fp32).
+// The bf16 matrix cores with cq as three terms took 27 us against 44 (49
+// sources, 48 sites, r = 256, 2048 tokens), but round long sums coarsely: in
+// one chain, the error grew with the tokens, to 1.6 times at 2048.
 struct WideDqArgs {
     const uint16_t *V;  // [S][N][d]
     const float *cq;    // [N][T][64]
@@ -647,18 +649,24 @@ __global__ __launch_bounds__(kBlock, 2) void wide_dq(WideDqArgs a)
                 a.cq + ((size_t)n * a.T + min(16 * mt + lc, a.T - 1)) * kAllMaxSources + 16 * g + 4 * ks);
     };
     auto use = [&](int g, int u) {
+        float x[4][4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float x[4];
-            widen(raw[u][e], x);
+        for (int e = 0; e < 4; ++e)
+            widen(raw[u][e], x[e]);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                if (16 * g >= a.first + 16 * mt + 15)
-                    continue;  // wave-uniform: no site of the tile reads the group
+        for (int mt = 0; mt < MT; ++mt) {
+            if (16 * g >= a.first + 16 * mt + 15)
+                continue;  // wave-uniform: no site of the tile reads the group
+            f32x4_t t[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int p = 0; p < 4; ++p)
-                    tok[mt][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[u][mt][e], x[p], tok[mt][p], 0, 0, 0);
-            }
+                    t[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        q[u][mt][e], x[e][p], e == 0 ? f32x4_t{0.0f, 0.0f, 0.0f, 0.0f} : t[p], 0, 0, 0);
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                tok[mt][p] += t[p];
         }
         if (g + 1 == ngroups)  // wave-uniform
 #pragma unroll
@@ -774,6 +782,7 @@ __global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
     };
     auto use = [&](int64_t n, int g, int u) {
         const float *c = a.cq + (size_t)n * kAllMaxSources + 16 * g;  // wave-uniform
+        float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -783,8 +792,11 @@ __global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
                 const float w = c[4 * k + e];
 #pragma unroll
                 for (int p = 0; p < 4; ++p)
-                    tok[p] = fmaf(w, x[p], tok[p]);
+                    t[p] = fmaf(w, x[p], t[p]);
             }
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            tok[p] += t[p];
         if (g + 1 == ngroups)  // wave-uniform
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -845,18 +857,18 @@ __global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
 // dQ[x] (+)= the shares of element x: a workgroup takes 64 elements, its wave
 // w the w-th quarter of the shares, eight interleaved chains of them, summed
 // pairwise, and the quarters add up in order (coalesced over the elements;
-// long chains of fp32 additions would lose a bit that the shares still have;
-// zeros without tokens).
+// zeros without tokens).  Sums in fp64, which the kernel's time doesn't show
+// (it waits for its loads): the shares keep what they have.
 template <bool ACC>
 __global__ __launch_bounds__(kBlock) void wide_dq_sum(const float *__restrict__ partial,
                                                       float *__restrict__ dQ, int shares, int n)
 {
-    __shared__ float red[kWaves][kWaveSize];
+    __shared__ double red[kWaves][kWaveSize];
     const int lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
     const int x = blockIdx.x * kWaveSize + lane;
     const int per = (shares + kWaves - 1) / kWaves;
     const int beg = wave * per, end = min(shares, beg + per);
-    float s[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (x < n) {
         int k = beg;
         for (; k + 8 <= end; k += 8) {
@@ -881,8 +893,8 @@ __global__ __launch_bounds__(kBlock) void wide_dq_sum(const float *__restrict__ 
     red[wave][lane] = s[0];
     __syncthreads();
     if (wave == 0 && x < n) {
-        const float t = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-        dQ[x] = ACC ? dQ[x] + t : t;
+        const double t = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+        dQ[x] = (float)(ACC ? dQ[x] + t : t);
     }
 }
 

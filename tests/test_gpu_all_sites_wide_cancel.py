@@ -92,3 +92,37 @@ def test_cancelling_value_gradients_keep_fp32_weights(dev, case, accumulate):  #
     err = np.abs(to_host(dV)[..., :d - r].astype(np.float64) - ref)
     worst = (err / ((16 + T) * U * mag + 2.0 ** -8 * np.abs(ref))).max(axis=(1, 2))
     assert worst.max() <= 1.0, f"error / bar by source: {worst}"
+
+
+def dq64(V, Q, dH, first, r, eps=1e-6):
+    """dQ [T, r] in fp64 by torch, one site at a time."""
+    X = V.double().transpose(0, 1).contiguous()          # [N, S, d]
+    k = X[..., X.shape[2] - r:]
+    kb = k / (k.square().mean(-1, keepdim=True) + eps).sqrt()
+    out = []
+    for j in range(Q.shape[0]):
+        x, b = X[:, :first + j], kb[:, :first + j]
+        a = torch.softmax((b * Q[j].double()).sum(-1), dim=1)
+        g = (x * dH[j].double()[:, None]).sum(-1)
+        ds = a * (g - (a * g).sum(1, keepdim=True))
+        out.append((ds[..., None] * b).sum((0, 1)))
+    return torch.stack(out)
+
+
+@pytest.mark.parametrize("S,N,d,r", [(64, 1500, 128, 72), (49, 2048, 256, 128)])
+def test_dq_is_no_further_off_than_site_by_site(dev, S, N, d, r):  # noqa: F811
+    """dQ of the one pass against the single-site calls' own distance from 64
+    bits: the same fp32 operations, the sum over sources and tokens split
+    differently (at these sizes 0.9 of their distance; with one chain of
+    additions over a token's sources and fp32 sums of the shares 1.05)."""
+    gen = torch.Generator().manual_seed(S + N)
+    T, first = S - 1, 2
+    scale = torch.exp2(torch.rand((S, 1, 1), generator=gen) * 3.0 - 1.5)
+    V = (torch.randn((S, N, d), generator=gen) * scale).to(torch.bfloat16).to(dev)
+    Q = (torch.randn((T, r), generator=gen) * 1.5 * r ** -0.5).to(dev)
+    dH = torch.randn((T, N, d), generator=gen).to(torch.bfloat16).to(dev)
+    ref = dq64(V, Q, dH, first, r)
+    _, _, dQ = lr.route_all_bwd(V, None, Q, dH, SLICED, first)
+    sites = torch.stack([lr.route_bwd(V[:first + j], None, Q[j], dH[j], SLICED)[2] for j in range(T)])
+    far, far_sites = (float((x.double() - ref).norm() / ref.norm()) for x in (dQ, sites))
+    assert far <= far_sites
