@@ -403,10 +403,12 @@ __global__ __launch_bounds__(kBlock) void route_neff(const T *__restrict__ keys,
 // whatever the number of tokens, sites or sources (49 sources, 48 sites,
 // d = 1024, r = 256: forward 2.1 ms -> 0.11 ms at 2048 tokens; the backward's
 // figures are with its kernels).  r % 8: key rows of whole 16-byte vectors.
+// Its kernels take a workgroup per token, and a launch holds less than 2^32
+// threads; more tokens go site by site, with four or more to a workgroup.
 bool all_wide(const AllProblem &p)
 {
     const int64_t koff = p.d - p.r;
-    return p.dtype == LRAR_DTYPE_BF16 && p.mode != LRAR_MODE_PROJECTED &&
+    return p.N * kBlock < ((int64_t)1 << 32) && p.dtype == LRAR_DTYPE_BF16 && p.mode != LRAR_MODE_PROJECTED &&
            (p.mode == LRAR_MODE_FULL || p.r > kAllMaxRank) && p.S <= kAllMaxSources &&
            p.T <= kAllMaxSources && p.d % 8 == 0 && koff % 8 == 0 &&
            reinterpret_cast<uintptr_t>(p.Q) % 16 == 0;

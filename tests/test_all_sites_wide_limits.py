@@ -37,3 +37,17 @@ def test_rank_above_the_backward_limit_stays_refused():
                                       100, 1024, 264, 2, 48, lr.SLICED, BF16,
                                       ctypes.c_float(1e-6), 0, None)
     assert rc == 2 and b"site by site" in lib.lr_attnres_last_error()
+
+
+@pytest.mark.parametrize("N,wide", [((1 << 24) - 1, True), (1 << 24, False), (1 << 30, False)])
+def test_tokens_past_one_launch_run_site_by_site(N, wide):
+    """The wide kernels take a 256-thread workgroup per token and a launch less
+    than 2^32 threads; calls with more tokens stay accepted."""
+    need = _workspace(32, N, 72, 72, 1, 32, BF16)
+    assert need > 0 and (need > N * 32 * 64 * 4) == wide
+    lib = lr.load_library()
+    a = [0x1000_0000_0000 * k for k in range(1, 7)]
+    rc = lib.lr_attnres_route_all_bwd(a[0], None, a[1], a[2], a[3], None, a[4], a[5], need - 1, 32,
+                                      N, 72, 72, 1, 32, lr.SLICED, BF16, ctypes.c_float(1e-6), 0,
+                                      None)
+    assert rc == 1 and b"workspace" in lib.lr_attnres_last_error()
