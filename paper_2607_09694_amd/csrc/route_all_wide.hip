@@ -941,8 +941,12 @@ namespace {
 
 // Tokens above which few sources take a wave per token: the quarters of its
 // rows then run one after the other, which costs a call of few tokens more
-// than the idle lanes of a workgroup per token do.
-constexpr int64_t kFullWaveTokens = 2048;
+// than the idle lanes of a workgroup per token do.  Workgroup per token ->
+// wave: one tile of sources, 2 of d = 1024: 256 tokens 16 -> 19 us, 400
+// level, 2048 50 -> 23; 16 of d = 512: 256 14 -> 14, 512 17 -> 16, 2048 46 ->
+// 26.  More tiles, 32 of d = 512: 800 tokens 25 -> 27, 1024 26 -> 28, 2048 52
+// -> 42; 64 of d = 256: 800 30 -> 28, 2048 51 -> 41.
+constexpr int64_t kFullWaveTokens = 320, kFullWaveTokensTiles = 1024;
 
 template <int HS, int NT, int TOK, bool ACC>
 void launch_rows(const WideBwdArgs &b, hipStream_t st)
@@ -958,7 +962,7 @@ template <int HS, bool ACC>
 void launch_rows_hs(const WideBwdArgs &b, hipStream_t st)
 {
     const int nt = (b.f.S + 15) / 16;
-    const bool many = b.f.N > kFullWaveTokens;
+    const bool many = b.f.N > (nt == 1 ? kFullWaveTokens : kFullWaveTokensTiles);
     if (many && b.f.S <= 4)
         return launch_rows<HS, 1, 4, ACC>(b, st);
     if (many && b.f.S <= 8)

@@ -171,3 +171,25 @@ def test_full_rank_single_site_of_many_tokens(dev, case, accumulate):  # noqa: F
     check_bf16_grown("dV", to_host(dV), rV)
     check_dq("dq", to_host(dq), rQ)
     assert torch.equal(dQ[0], dq)
+
+
+# (N, d): both sides of the tokens from which a single site takes a wave per
+# token, with one tile of sources (320) and with more (1024), for every width.
+SINGLE_SITES = [(319, 136), (321, 1000), (321, 264), (1024, 200), (1025, 200), (1025, 456),
+                (2053, 1024)]
+
+
+@pytest.mark.parametrize("N,d", SINGLE_SITES)
+def test_full_rank_rows_of_one_pass_are_the_single_sites(dev, N, d):  # noqa: F811
+    """Every dQ row of one pass over the stack is bit for bit the single-site
+    dq of its site: 2 to 4 sources (a wave shared by four tokens), to 8, to 16,
+    to 32 and above."""
+    S, first = 50, 2
+    T = S - first + 1
+    _, _, _, V, Qd, dHd = _run(dev, (S, T, first, N, d, d), seed=N + d)
+    _, _, dQ = lr.route_all_bwd(V, None, Qd, dHd, FULL, first)
+    for n_src in (2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 48, 49, 50):
+        j = n_src - first
+        _, _, dq = lr.route_bwd(V[:n_src], None, Qd[j].contiguous(), dHd[j], FULL)
+        torch.cuda.synchronize()
+        assert torch.equal(dQ[j], dq), f"{n_src} sources"
