@@ -399,12 +399,10 @@ __global__ __launch_bounds__(kBlock) void route_neff(const T *__restrict__ keys,
 
 }  // namespace
 
-// Wide keys: one pass over the stack for all sites instead of one per site,
-// whatever the number of tokens, sites or sources (49 sources, 48 sites,
-// d = 1024, r = 256: forward 2.1 ms -> 0.11 ms at 2048 tokens; the backward's
-// figures are with its kernels).  r % 8: key rows of whole 16-byte vectors.
-// Its kernels take a workgroup per token, and a launch holds less than 2^32
-// threads; more tokens go site by site, with four or more to a workgroup.
+// Wide keys, one pass over the stack for all sites instead of one per site.
+// r % 8: key rows of whole 16-byte vectors.  The kernels take a workgroup per
+// token, and a launch holds less than 2^32 threads; more tokens go site by
+// site, with four or more to a workgroup.
 bool all_wide(const AllProblem &p)
 {
     const int64_t koff = p.d - p.r;
@@ -412,6 +410,43 @@ bool all_wide(const AllProblem &p)
            (p.mode == LRAR_MODE_FULL || p.r > kAllMaxRank) && p.S <= kAllMaxSources &&
            p.T <= kAllMaxSources && p.d % 8 == 0 && koff % 8 == 0 &&
            reinterpret_cast<uintptr_t>(p.Q) % 16 == 0;
+}
+
+namespace {
+
+// Source rows that the sites read one by one.
+int64_t site_reads(const AllProblem &p) { return p.T * p.first + p.T * (p.T - 1) / 2; }
+
+}  // namespace
+
+// Where one pass over the stack is ahead of the sites one by one: its time
+// goes with the tokens (a workgroup's phases), theirs with the sites and the
+// rows that these read, less so while a launch of few tokens waits for its
+// latency.  Site by site -> one pass, in us:
+//   forward, sliced r = 72: 8192 tokens, d = 136: 8 sources, 7 sites 142 ->
+//   125; 24, 3 126 -> 130; 12, 4 108 -> 126; 49, 2 152 -> 148; 49, 1 79 -> 147;
+//   48 sites of d = 1024, r = 256, 2048 tokens: 2100 -> 113.  At 2048 tokens
+//   16 sources, 2 sites are 1.07x, 12, 2 0.99x, 6, 2 0.85x; at 300 one site is
+//   1.01 to 1.17x (it saves the launch of N_eff);
+//   backward, accumulating, full rank: 8192 tokens, d = 136: 12 sources, 11
+//   sites 361 -> 256; 49, 3 398 -> 373; 24, 3 210 -> 294; 8, 7 197 -> 249; 49, 2
+//   270 -> 369.  At 2048 tokens 12 sources, 4 sites are 0.99 to 1.2x, 8, 7 1.2x,
+//   16, 3 0.8x, 6, 5 0.74x, 49, 2 0.84x.  Sliced, 1100 tokens: 6, 5 1.1x, 8, 4
+//   0.98x, 4, 3 0.6x (overwriting, where the sites need a zero fill, 1.4x, 1.3x,
+//   0.8x; and one pass rounds each gradient once, not after every site).
+//   Full-rank sites have their rows in registers and stay ahead for longer
+//   (6, 5 0.85x, 8, 4 0.88x).
+bool wide_fwd_pays(const AllProblem &p)
+{
+    return p.N <= 256 || (p.T >= 2 && 8 * p.T + site_reads(p) >= (p.N <= 2048 ? 40 : 90));
+}
+
+bool wide_bwd_pays(const AllProblem &p)
+{
+    const int64_t w = 10 * p.T + site_reads(p);
+    if (p.T < 3 || p.N > 2048)
+        return p.T >= 3 && w >= 160;
+    return w >= (p.mode == LRAR_MODE_FULL || p.N > 1280 ? 80 : 50);
 }
 
 bool all_fused(const AllProblem &p)
@@ -435,8 +470,9 @@ int check_all_supported(const AllProblem &p, std::string *why)
     if (all_fused(p))
         return LRAR_OK;
     // Full-rank keys, wide keys, or more than 64 sources or sites (the wide
-    // launch takes no more than the sites do): site by site, each site as the single-site forward over its prefix.
-    // The last site reads the most sources and binds.
+    // launch takes no more than the sites do): site by site, each site as the
+    // single-site forward over its prefix.  The last site reads the most
+    // sources and binds.
     std::string w;
     if (check_supported(all_site_problem(p, p.T - 1), false, &w) != LRAR_OK) {
         *why = "all-sites routing, site by site: " + w;
@@ -449,7 +485,8 @@ int launch_all_fwd(const AllProblem &p, hipStream_t st, std::string *err)
 {
     if (p.N == 0)
         return LRAR_OK;
-    if (all_wide(p) && (p.mode != LRAR_MODE_FULL || p.N > kFullSitesOneByOne)) {
+    if (all_wide(p) && wide_fwd_pays(p) &&
+        (p.mode != LRAR_MODE_FULL || p.N > kFullSitesOneByOne)) {
         const AllArgs a = all_wide_args(p);
         const dim3 grid((unsigned)p.N), block(kBlock);
         switch ((a.T + 15) / 16) {

@@ -595,6 +595,9 @@ namespace {
 // The fused backward takes bf16 storage and what the fused forward takes.
 bool all_bwd_fused(const AllProblem &p) { return p.dtype == LRAR_DTYPE_BF16 && all_fused(p); }
 
+// The wide backward, for problems that the sites take one by one as well.
+bool all_bwd_wide(const AllProblem &p) { return p.N > 0 && all_wide(p) && wide_bwd_pays(p); }
+
 __global__ void __launch_bounds__(256) fill_zero16(u32x4_t *__restrict__ p, size_t n)
 {
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
@@ -636,7 +639,7 @@ size_t all_bwd_workspace_bytes(const AllProblem &p)
         // run site by site (an unaligned Q); the last site's workspace covers
         // all full-rank sites at once.
         const size_t site = bwd_workspace_bytes(all_site_problem(p, p.T - 1));
-        return site > 0 && p.mode == LRAR_MODE_SLICED && all_wide(p)
+        return site > 0 && p.mode == LRAR_MODE_SLICED && all_bwd_wide(p)
                    ? std::max(site, wide_bwd_workspace_bytes(p.N, p.T, p.r))
                    : site;
     }
@@ -652,7 +655,8 @@ int check_all_bwd_supported(const AllProblem &p, std::string *why)
     if (all_bwd_fused(p))
         return LRAR_OK;
     // Full-rank keys, fp32 storage, wide keys, or more than 64 sources or
-    // sites (the wide launch takes no more than the sites do): site by site, each site's accumulating single-site backward.
+    // sites (the wide launch takes no more than the sites do): site by site,
+    // each site's accumulating single-site backward.
     std::string w;
     if (check_supported(all_site_problem(p, p.T - 1), true, &w) != LRAR_OK) {
         *why = "all-sites backward, site by site: " + w;
@@ -664,13 +668,15 @@ int check_all_bwd_supported(const AllProblem &p, std::string *why)
 int launch_all_bwd(const AllProblem &p, const void *dH, void *dV, void *dK, float *dQ, void *ws,
                    bool accumulate, hipStream_t st, std::string *err)
 {
-    if (all_wide(p) && all_bwd_workspace_bytes(p) >= wide_bwd_workspace_bytes(p.N, p.T, p.r))
+    if (all_bwd_wide(p))
         return launch_wide_bwd(p, dH, dV, dQ, ws, accumulate, st, err);
     if (!all_bwd_fused(p)) {
         // Site by site: each site's backward adds into the gradients of its
-        // prefix and into its row of dQ, after one zero fill when overwriting.
+        // prefix and into its row of dQ, after one zero fill when overwriting
+        // (one site that reads the whole stack overwrites by itself).
         const size_t es = p.dtype == LRAR_DTYPE_BF16 ? 2 : 4;
-        if (!accumulate) {
+        const bool add = accumulate || p.T > 1 || p.first < p.S;
+        if (add && !accumulate) {
             hipError_t e = launch_zero(dV, (size_t)p.S * p.N * p.d * es, st);
             if (e == hipSuccess && p.mode == LRAR_MODE_PROJECTED)
                 e = launch_zero(dK, (size_t)p.S * p.N * p.r * es, st);
@@ -683,7 +689,7 @@ int launch_all_bwd(const AllProblem &p, const void *dH, void *dV, void *dK, floa
             const int rc = launch_bwd(all_site_problem(p, j),
                                       static_cast<const char *>(dH) + (size_t)j * p.N * p.d * es,
                                       dV, dK, dQ + j * p.r, ws, all_bwd_workspace_bytes(p),
-                                      true, st, err);
+                                      add, st, err);
             if (rc != LRAR_OK)
                 return rc;
         }

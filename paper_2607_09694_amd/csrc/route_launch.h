@@ -171,6 +171,9 @@ bool all_fused(const AllProblem &p);
 // Whether the fused kernels of wide keys take it (bf16 storage, sliced keys
 // of more than 64 columns or full-rank keys, S and T <= 64, 16-byte key rows).
 bool all_wide(const AllProblem &p);
+// And whether they are ahead of the sites one by one.
+bool wide_fwd_pays(const AllProblem &p);
+bool wide_bwd_pays(const AllProblem &p);
 // Their backward; the workspace is 4-byte aligned, dK does not exist.
 size_t wide_bwd_workspace_bytes(int64_t N, int64_t T, int64_t r);
 // Widest full-rank row that the single-site form keeps in registers.

@@ -51,3 +51,18 @@ def test_tokens_past_one_launch_run_site_by_site(N, wide):
                                       N, 72, 72, 1, 32, lr.SLICED, BF16, ctypes.c_float(1e-6), 0,
                                       None)
     assert rc == 1 and b"workspace" in lib.lr_attnres_last_error()
+
+
+@pytest.mark.parametrize("S,N,first,T,wide", [
+    (12, 2048, 9, 4, True), (12, 2049, 9, 4, False),      # 42 reads, 4 sites
+    (12, 2049, 2, 11, True),
+    (6, 1280, 2, 5, True), (6, 1281, 2, 5, False), (4, 1280, 2, 3, False),
+    (64, 2048, 63, 2, False), (64, 2048, 64, 1, False),   # fewer than three sites
+    (49, 8192, 47, 3, True), (24, 2049, 22, 3, False),
+])
+def test_few_sites_run_one_by_one(S, N, first, T, wide):
+    """One pass over the stack only where it is ahead of the sites: few reads
+    of the stack keep the single site's workspace."""
+    need = _workspace(S, N, 1024, 256, first, T, BF16)
+    single = lr.load_library().lr_attnres_route_bwd_workspace_bytes(S, N, 1024, 256, lr.SLICED, BF16)
+    assert (need == single) != wide and (need > N * T * 64 * 4) == wide
