@@ -1004,6 +1004,19 @@ bool launch_full_rows(const WideBwdArgs &b, hipStream_t st)
 
 }  // namespace
 
+// Rows of 1024 columns, which route_bwd_full takes without column masks, leave
+// the register form level with it at 32 sources and behind with fewer from
+// about 16384 tokens on (route_bwd_full -> this: 16001 tokens, 4 sources 103 ->
+// 101 us, 16: 357 -> 317; 24000 tokens, 2: 84 -> 107, 16: 411 -> 460, 32: 898 ->
+// 898; 60001 tokens, 16: 986 -> 1115).  Rows of 1000 columns gain throughout
+// (60001 tokens, 2: 285 -> 283, 16: 1463 -> 1251).
+bool full_rows(const Problem &p)
+{
+    return p.mode == LRAR_MODE_FULL && p.dtype == LRAR_DTYPE_BF16 && p.d % 8 == 0 &&
+           p.d <= kFullRowsMax && (p.d < kFullRowsMax || p.N <= 16384) &&
+           p.N * kBlock < ((int64_t)1 << 32);
+}
+
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
                     bool accumulate, hipStream_t st, std::string *err)
 {

@@ -26,7 +26,9 @@ struct Problem {
 // LRAR_EUNSUPPORTED with the reason in *why.  No HIP call.
 int check_supported(const Problem &p, bool bwd, std::string *why);
 
-// Workspace of the backward (per-workgroup dq partials).  No HIP call.
+// Workspace of the backward (per-workgroup dq partials, or what the register
+// form of full-rank keys needs where that is more); the same for every number
+// of sources.  No HIP call.
 size_t bwd_workspace_bytes(const Problem &p);
 // The dq partials alone (what every form but full rank's matrix-core one needs).
 size_t bwd_partial_bytes(const Problem &p);
@@ -176,8 +178,10 @@ bool wide_fwd_pays(const AllProblem &p);
 bool wide_bwd_pays(const AllProblem &p);
 // Their backward; the workspace is 4-byte aligned, dK does not exist.
 size_t wide_bwd_workspace_bytes(int64_t N, int64_t T, int64_t r);
-// Widest full-rank row that the single-site form keeps in registers.
+// Widest full-rank row that the single-site form keeps in registers, and
+// whether storage, keys and rows suit that form (2 to 64 sources take it).
 constexpr int64_t kFullRowsMax = 1024;
+bool full_rows(const Problem &p);
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
                     bool accumulate, hipStream_t st, std::string *err);
 // The single-site problem of site j of an all-sites problem.
