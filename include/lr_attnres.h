@@ -87,8 +87,10 @@ int lr_attnres_route_fwd(const void *V, const void *K, const float *q, void *H,
 
 /*
  * Bytes of device workspace lr_attnres_route_bwd needs for this problem
- * (per-workgroup partial sums of dq; for full-rank keys in bf16 the softmax
- * gradients of every token, where that is more).  0 for an invalid problem.
+ * (per-workgroup partial sums of dq; for full-rank keys in bf16 and d <= 1024
+ * the softmax gradients of the site, 256 bytes per token, and shares of dq,
+ * where that is more).  The same for every number of sources.  0 for an
+ * invalid problem.
  */
 size_t lr_attnres_route_bwd_workspace_bytes(int64_t S, int64_t N, int64_t d, int64_t r,
                                             int mode, int dtype);

@@ -635,11 +635,10 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st)
 size_t all_bwd_workspace_bytes(const AllProblem &p)
 {
     if (!all_bwd_fused(p)) {
-        // 0 where the call is refused or has no tokens.  Wide keys may still
-        // run site by site (an unaligned Q); the last site's workspace covers
-        // all full-rank sites at once.
+        // 0 where the call is refused or has no tokens.  A problem of the wide
+        // kernels may still run site by site (an unaligned Q).
         const size_t site = bwd_workspace_bytes(all_site_problem(p, p.T - 1));
-        return site > 0 && p.mode == LRAR_MODE_SLICED && all_bwd_wide(p)
+        return site > 0 && all_bwd_wide(p)
                    ? std::max(site, wide_bwd_workspace_bytes(p.N, p.T, p.r))
                    : site;
     }

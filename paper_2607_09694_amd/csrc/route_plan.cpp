@@ -141,9 +141,14 @@ int check_supported(const Problem &p, bool bwd, std::string *why)
 
 size_t bwd_partial_bytes(const Problem &p)
 {
+    // Of a site of two sources or more: one source alone may need fewer rows
+    // (plan: its token is not split), but a buffer sized for the first site of
+    // a pass serves them all.
+    Problem q = p;
+    q.S = std::max<int64_t>(p.S, 2);
     Plan pl;
     std::string why;
-    if (!make_plan(p, true, &pl, &why))
+    if (!make_plan(q, true, &pl, &why))
         return 0;
     const int64_t ncols = p.mode == LRAR_MODE_FULL ? p.d : p.r;
     return (size_t)pl.nblocks * (size_t)ncols * sizeof(float);
@@ -151,15 +156,10 @@ size_t bwd_partial_bytes(const Problem &p)
 
 size_t bwd_workspace_bytes(const Problem &p)
 {
-    // Full rank: enough for every site of a pass that ends with this one, so
-    // that the single-site and the all-sites call share one size (S sites at
-    // most).  Also where S is past what the matrix-core form takes: the first
-    // sites of such a pass take it.  One source never does (its weight is 1
-    // and its dq 0).
+    // The register form of full-rank keys where the call can take it, whatever
+    // the number of sources (as the partials: the same for every site).
     const size_t need = bwd_partial_bytes(p);
-    const bool wide = p.mode == LRAR_MODE_FULL && p.dtype == LRAR_DTYPE_BF16 && p.d % 8 == 0 &&
-                      p.S > 1;
-    return need > 0 && wide ? std::max(need, wide_bwd_workspace_bytes(p.N, std::min<int64_t>(p.S, 64), p.d)) : need;
+    return need > 0 && full_rows(p) ? std::max(need, wide_bwd_workspace_bytes(p.N, 1, p.d)) : need;
 }
 
 }  // namespace lrar

@@ -66,3 +66,31 @@ def test_few_sites_run_one_by_one(S, N, first, T, wide):
     need = _workspace(S, N, 1024, 256, first, T, BF16)
     single = lr.load_library().lr_attnres_route_bwd_workspace_bytes(S, N, 1024, 256, lr.SLICED, BF16)
     assert (need == single) != wide and (need > N * T * 64 * 4) == wide
+
+
+def _single(S, N, d, r, mode, dtype):
+    return lr.load_library().lr_attnres_route_bwd_workspace_bytes(S, N, d, r, mode, dtype)
+
+
+@pytest.mark.parametrize("S,N,d,shares", [
+    (49, 16384, 1024, 64), (2, 16384, 1024, 64), (64, 100000, 64, 1024), (100, 1000, 512, 128),
+])
+def test_one_full_rank_site_asks_for_one_site(S, N, d, shares):
+    """The softmax gradients of each token at one site and the dq shares, or
+    the dq partials of a workgroup per 16 (few tokens: 4 or 8) tokens."""
+    rows = 16 + (N * 64 + shares * d) * 4
+    assert rows <= _single(S, N, d, d, lr.FULL, BF16) <= max(rows, -(-N // 4) * d * 4)
+
+
+@pytest.mark.parametrize("S,N,d,dtype", [(64, 16384, 2048, BF16), (49, 16384, 1020, BF16), (49, 16385, 1024, BF16),
+                                         (49, 16384, 1024, F32), (49, 1 << 24, 64, BF16)])
+def test_full_rank_sites_of_other_forms_ask_for_dq_partials(S, N, d, dtype):
+    assert _single(S, N, d, d, lr.FULL, dtype) == -(-N // 16) * d * 4
+
+
+@pytest.mark.parametrize("mode,d,r,dtype", [(lr.PROJECTED, 256, 16, BF16), (lr.SLICED, 256, 16, F32),
+                                            (lr.FULL, 512, 512, BF16), (lr.FULL, 512, 512, F32)])
+@pytest.mark.parametrize("N", [1, 300, 512, 513, 5000])
+def test_workspace_is_the_same_for_every_number_of_sources(mode, d, r, dtype, N):
+    """A buffer sized for the first site of a pass serves the later ones."""
+    assert len({_single(S, N, d, r, mode, dtype) for S in (1, 2, 3, 64, 65, 512)}) == 1
