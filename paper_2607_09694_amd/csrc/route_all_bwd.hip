@@ -668,7 +668,7 @@ int launch_all_bwd(const AllProblem &p, const void *dH, void *dV, void *dK, floa
                    bool accumulate, hipStream_t st, std::string *err)
 {
     if (all_bwd_wide(p))
-        return launch_wide_bwd(p, dH, dV, dQ, ws, accumulate, st, err);
+        return launch_wide_bwd(p, dH, dV, dQ, ws, all_bwd_workspace_bytes(p), accumulate, st, err);
     if (!all_bwd_fused(p)) {
         // Site by site: each site's backward adds into the gradients of its
         // prefix and into its row of dQ, after one zero fill when overwriting

@@ -57,6 +57,7 @@ struct WideBwdArgs {
     const uint16_t *dH;  // [T][N][d]
     uint16_t *dV;        // [sources][N][d]
     float *cq;           // [N][T][64] ds / rho
+    int64_t n0 = 0, n1 = 0;  // route_bwd_full_rows: its tokens (cq from the first on)
 };
 
 // One slab of dV (or its key term) summed over the reading sites only, on the
@@ -361,9 +362,10 @@ __global__ __launch_bounds__(kBlock, 2) void route_bwd_full_rows(WideBwdArgs b)
     // The lane's token (the wave's first for P = 1) and its source in a tile;
     // lanes past the tokens re-read the last one and store nothing.
     const int tl = lc / GL, il = lc % GL;
-    const int64_t nw = WAVE ? ((int64_t)xcd_block().x * kWaves + wave) * P : xcd_block().x;
-    const bool live = nw + tl < a.N;
-    const int64_t n = min(nw + tl, a.N - 1);
+    const int64_t nw =
+        b.n0 + (WAVE ? ((int64_t)xcd_block().x * kWaves + wave) * P : xcd_block().x);
+    const bool live = nw + tl < b.n1;
+    const int64_t n = min(nw + tl, b.n1 - 1);
     uint16_t *const hs = hall + (WAVE ? wave * P * kCols : 0);
     const size_t plane = (size_t)a.N * a.d;
     // This lane's columns of step s of quarter k; a quarter has 2 per <= HS
@@ -387,7 +389,7 @@ __global__ __launch_bounds__(kBlock, 2) void route_bwd_full_rows(WideBwdArgs b)
 #pragma unroll
         for (int k = 0; k < kHl; ++k) {
             const int c = h4 + 4 * kWaveSize * k;
-            ht[t][k] = load_raw<uint16_t, 4>(b.dH + min(nw + t, a.N - 1) * a.d + min(c, a.d - 4));
+            ht[t][k] = load_raw<uint16_t, 4>(b.dH + min(nw + t, b.n1 - 1) * a.d + min(c, a.d - 4));
             if (c >= a.d)
                 ht[t][k] = u32x2_t{0u, 0u};
         }
@@ -511,7 +513,7 @@ __global__ __launch_bounds__(kBlock, 2) void route_bwd_full_rows(WideBwdArgs b)
         if ((WAVE ? live : wave == 0) && ks == 0)
 #pragma unroll
             for (int k = 0; k < kAllMaxSources / GL; ++k)
-                b.cq[(size_t)n * kAllMaxSources + GL * k + il] = k < NT ? cq[k < NT ? k : 0][0] : 0.0f;
+                b.cq[(size_t)(n - b.n0) * kAllMaxSources + GL * k + il] = k < NT ? cq[k < NT ? k : 0][0] : 0.0f;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             al_i[nt] = __shfl(al[nt][0], lc, kWaveSize);
@@ -589,6 +591,11 @@ struct WideDqArgs {
     float *partial;     // [gridDim.y][T][r]
     int S, d, r, first, T;
     int64_t N;
+    // wide_dq_one: its tokens (cq from the first on), and where the waves' sums
+    // [gridDim.y][4][r] pass from one range of tokens to the next (NULL for one
+    // range).
+    int64_t n0 = 0, n1 = 0;
+    float *carry = nullptr;
 };
 
 // The same share over each site's prefix only, on the vector units (a
@@ -770,7 +777,7 @@ __global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
     const bool ok = c0 < a.r;
     const size_t plane = (size_t)a.N * a.d;
     const uint16_t *key = a.V + (a.d - a.r) + (ok ? c0 : 0);
-    const int64_t n0 = (int64_t)blk.y * kWaves + wave, step = (int64_t)gridDim.y * kWaves;
+    const int64_t n0 = a.n0 + (int64_t)blk.y * kWaves + wave, step = (int64_t)gridDim.y * kWaves;
     const int ngroups = (a.S + 15) / 16;
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, tok[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     u32x2_t raw[AHEAD][4 * K4];
@@ -781,7 +788,7 @@ __global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
             raw[u][i] = load_stream<uint16_t, 4, true>(r0 + (size_t)min(16 * g + i, a.S - 1) * plane);
     };
     auto use = [&](int64_t n, int g, int u) {
-        const float *c = a.cq + (size_t)n * kAllMaxSources + 16 * g;  // wave-uniform
+        const float *c = a.cq + (size_t)(n - a.n0) * kAllMaxSources + 16 * g;  // wave-uniform
         float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -804,7 +811,7 @@ __global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
                 tok[p] = 0.0f;
             }
     };
-    const int64_t total = n0 < a.N ? ((a.N - n0 + step - 1) / step) * ngroups : 0;
+    const int64_t total = n0 < a.n1 ? ((a.n1 - n0 + step - 1) / step) * ngroups : 0;
     int64_t nl = n0, nu = n0;  // token and group of the next load and of the next use
     int gl = 0, gu = 0;
     auto advance = [&]() {
@@ -812,11 +819,19 @@ __global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
             gl = 0;
             nl += step;
         }
-        if (nl >= a.N) {
+        if (nl >= a.n1) {
             nl -= step;
             gl = ngroups - 1;
         }
     };
+    f32x4_t *carry =
+        reinterpret_cast<f32x4_t *>(a.carry + ((size_t)blk.y * kWaves + wave) * a.r + c0);
+    if (a.carry && a.n0 > 0 && ok) {
+        const f32x4_t v = *carry;
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            acc[p] = v[p];
+    }
     if (total > 0) {
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) {
@@ -839,6 +854,11 @@ __global__ __launch_bounds__(kBlock) void wide_dq_one(WideDqArgs a)
             load(nl, gl, u);
             advance();
         }
+    if (a.carry && a.n1 < a.N) {  // uniform: more tokens follow
+        if (ok)
+            *carry = f32x4_t{acc[0], acc[1], acc[2], acc[3]};
+        return;
+    }
     if (wave > 0)
         *reinterpret_cast<f32x4_t *>(red + (wave - 1) * kDqOneSlab + 4 * lane) =
             f32x4_t{acc[0], acc[1], acc[2], acc[3]};
@@ -900,24 +920,25 @@ __global__ __launch_bounds__(kBlock) void wide_dq_sum(const float *__restrict__ 
 
 template <int MT>
 void launch_wide_mt(const WideBwdArgs &b, const WideDqArgs &q, dim3 qgrid, bool accumulate,
-                    bool rows, hipStream_t st)
+                    hipStream_t st)
 {
     const dim3 grid((unsigned)b.f.N), block(kBlock);
-    if (!rows) {
-        if (accumulate)
-            hipLaunchKernelGGL((route_all_bwd_wide<MT, true>), grid, block, 0, st, b);
-        else
-            hipLaunchKernelGGL((route_all_bwd_wide<MT, false>), grid, block, 0, st, b);
-    }
-    const dim3 one((unsigned)((q.r + kDqOneSlab - 1) / kDqOneSlab), qgrid.y);
-    if (q.T == 1 && q.S <= 4)
-        hipLaunchKernelGGL(wide_dq_one<1>, one, block, 0, st, q);
-    else if (q.T == 1 && q.S <= 8)
-        hipLaunchKernelGGL(wide_dq_one<2>, one, block, 0, st, q);
-    else if (q.T == 1)
-        hipLaunchKernelGGL(wide_dq_one<4>, one, block, 0, st, q);
+    if (accumulate)
+        hipLaunchKernelGGL((route_all_bwd_wide<MT, true>), grid, block, 0, st, b);
     else
-        hipLaunchKernelGGL(wide_dq<MT>, qgrid, block, 0, st, q);
+        hipLaunchKernelGGL((route_all_bwd_wide<MT, false>), grid, block, 0, st, b);
+    hipLaunchKernelGGL(wide_dq<MT>, qgrid, block, 0, st, q);
+}
+
+void launch_dq_one(const WideDqArgs &q, int64_t shares, hipStream_t st)
+{
+    const dim3 grid((unsigned)((q.r + kDqOneSlab - 1) / kDqOneSlab), (unsigned)shares), block(kBlock);
+    if (q.S <= 4)
+        hipLaunchKernelGGL(wide_dq_one<1>, grid, block, 0, st, q);
+    else if (q.S <= 8)
+        hipLaunchKernelGGL(wide_dq_one<2>, grid, block, 0, st, q);
+    else
+        hipLaunchKernelGGL(wide_dq_one<4>, grid, block, 0, st, q);
 }
 
 // Token shares of wide_dq: about four workgroups per CU over all key slabs,
@@ -953,7 +974,7 @@ void launch_rows(const WideBwdArgs &b, hipStream_t st)
 {
     constexpr int per = TOK > 0 ? TOK * kWaves : 1;  // tokens per workgroup
     hipLaunchKernelGGL((route_bwd_full_rows<HS, NT, TOK, ACC>),
-                       dim3((unsigned)((b.f.N + per - 1) / per)), dim3(kBlock), 0, st, b);
+                       dim3((unsigned)((b.n1 - b.n0 + per - 1) / per)), dim3(kBlock), 0, st, b);
 }
 
 // HS for the row width; a wave holds at most 32 vectors a lane of its rows, so
@@ -985,21 +1006,16 @@ void launch_rows_hs(const WideBwdArgs &b, hipStream_t st)
 }
 
 // The single site of full-rank keys with its rows in registers, up to
-// kFullRowsMax columns; false for others, which the all-sites kernel takes (wider rows
-// don't fit the registers; there it reads them twice).
+// kFullRowsMax columns.
 template <bool ACC>
-bool launch_full_rows(const WideBwdArgs &b, hipStream_t st)
+void launch_full_rows(const WideBwdArgs &b, hipStream_t st)
 {
-    const AllArgs &a = b.f;
-    if (a.T != 1 || a.koff != 0 || a.S != b.sources || a.d > kFullRowsMax)
-        return false;
-    if (a.d <= 256)
+    if (b.f.d <= 256)
         launch_rows_hs<2, ACC>(b, st);
-    else if (a.d <= 512)
+    else if (b.f.d <= 512)
         launch_rows_hs<4, ACC>(b, st);
     else
         launch_rows_hs<8, ACC>(b, st);
-    return true;
 }
 
 }  // namespace
@@ -1018,12 +1034,31 @@ bool full_rows(const Problem &p)
 }
 
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
-                    bool accumulate, hipStream_t st, std::string *err)
+                    size_t ws_bytes, bool accumulate, hipStream_t st, std::string *err)
 {
     const int64_t shares = wide_shares(p.N, p.r);
     float *cq = reinterpret_cast<float *>((reinterpret_cast<uintptr_t>(ws) + 15) / 16 * 16);
-    float *partial = cq + (size_t)p.N * p.T * kAllMaxSources;
+    float *partial = nullptr;
     if (p.N > 0) {
+        // The tokens go in one range where the workspace holds their cq.  For
+        // one site (the only caller with less, the allocation-free backward)
+        // they go in ranges of whole rounds over the shares, and the waves'
+        // sums pass on in between: the same additions in the same order.
+        const bool one = p.T == 1;
+        int64_t range = p.N;
+        size_t carry = 0;
+        if (one && ws_bytes < wide_bwd_workspace_bytes(p.N, 1, p.r)) {
+            const int64_t round = shares * kWaves;
+            carry = (size_t)round * p.r;
+            const int64_t room = (int64_t)((ws_bytes - 16) / sizeof(float)) -
+                                 (int64_t)(carry + (size_t)shares * p.r);
+            range = room / kAllMaxSources / round * round;
+            if (range <= 0) {
+                *err = "workspace too small for the full-rank backward";
+                return LRAR_EINVAL;
+            }
+        }
+        partial = cq + (size_t)range * p.T * kAllMaxSources;
         WideBwdArgs b;
         b.f = all_wide_args(p);
         b.f.H = nullptr;
@@ -1032,15 +1067,23 @@ int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, vo
         b.dH = static_cast<const uint16_t *>(dH);
         b.dV = static_cast<uint16_t *>(dV);
         b.cq = cq;
-        const WideDqArgs q{static_cast<const uint16_t *>(p.V), cq, partial, b.f.S, (int)p.d,
-                           (int)p.r, b.f.first, b.f.T, p.N};
+        WideDqArgs q{static_cast<const uint16_t *>(p.V), cq, partial, b.f.S, (int)p.d,
+                     (int)p.r, b.f.first, b.f.T, p.N};
+        if (carry)
+            q.carry = partial + (size_t)shares * p.r;
         const dim3 qgrid((unsigned)((p.r + kDqSlab - 1) / kDqSlab), (unsigned)shares);
-        const bool rows = accumulate ? launch_full_rows<true>(b, st) : launch_full_rows<false>(b, st);
-        switch ((b.f.T + 15) / 16) {
-        case 1: launch_wide_mt<1>(b, q, qgrid, accumulate, rows, st); break;
-        case 2: launch_wide_mt<2>(b, q, qgrid, accumulate, rows, st); break;
-        case 3: launch_wide_mt<3>(b, q, qgrid, accumulate, rows, st); break;
-        default: launch_wide_mt<4>(b, q, qgrid, accumulate, rows, st); break;
+        for (int64_t n = 0; one && n < p.N; n += range) {
+            b.n0 = q.n0 = n;
+            b.n1 = q.n1 = std::min(p.N, n + range);
+            accumulate ? launch_full_rows<true>(b, st) : launch_full_rows<false>(b, st);
+            launch_dq_one(q, shares, st);
+        }
+        switch (one ? 0 : (b.f.T + 15) / 16) {
+        case 0: break;
+        case 1: launch_wide_mt<1>(b, q, qgrid, accumulate, st); break;
+        case 2: launch_wide_mt<2>(b, q, qgrid, accumulate, st); break;
+        case 3: launch_wide_mt<3>(b, q, qgrid, accumulate, st); break;
+        default: launch_wide_mt<4>(b, q, qgrid, accumulate, st); break;
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)

@@ -267,9 +267,8 @@ int launch_bwd(const Problem &p, const void *dH, void *dV, void *dK, float *dq, 
     // tokens).
     const AllProblem one{p.V, p.K, p.q, nullptr, nullptr, p.S, p.N, p.d, p.r, p.S, 1,
                          p.mode, p.dtype, p.eps};
-    if (p.N > 0 && p.S > 1 && full_rows(p) && all_wide(one) &&
-        ws_bytes >= wide_bwd_workspace_bytes(p.N, 1, p.d))
-        return launch_wide_bwd(one, dH, dV, dq, ws, accumulate, st, err);
+    if (p.N > 0 && p.S > 1 && full_rows(p) && all_wide(one))
+        return launch_wide_bwd(one, dH, dV, dq, ws, ws_bytes, accumulate, st, err);
     float *partial = static_cast<float *>(ws);
     const hipError_t e =
         accumulate ? launch_bwd_acc<true, true>(p, pl, dH, dV, dK, dq, partial, st)

@@ -42,8 +42,6 @@ int launch_state(const Problem &p, int64_t chunk, float *M, float *L, float *ACC
 int launch_merge(const float *M, const float *L, const float *ACC, int64_t P, int64_t N, int64_t d,
                  int dtype, void *H, hipStream_t st, std::string *err);
 // accumulate: add the gradients into dV, dK and dq instead of overwriting.
-// ws_bytes: full-rank keys take the matrix-core form where it holds that
-// form's workspace, which bwd_workspace_bytes(p) always does.
 int launch_bwd(const Problem &p, const void *dH, void *dV, void *dK, float *dq, void *ws,
                size_t ws_bytes, bool accumulate, hipStream_t st, std::string *err);
 
@@ -176,14 +174,16 @@ bool all_wide(const AllProblem &p);
 // And whether they are ahead of the sites one by one.
 bool wide_fwd_pays(const AllProblem &p);
 bool wide_bwd_pays(const AllProblem &p);
-// Their backward; the workspace is 4-byte aligned, dK does not exist.
+// Their backward; the workspace is 4-byte aligned, dK does not exist.  One
+// site (full_rows: the register form) also takes less workspace than the
+// query, in ranges of tokens and with the same bits.
 size_t wide_bwd_workspace_bytes(int64_t N, int64_t T, int64_t r);
 // Widest full-rank row that the single-site form keeps in registers, and
 // whether storage, keys and rows suit that form (2 to 64 sources take it).
 constexpr int64_t kFullRowsMax = 1024;
 bool full_rows(const Problem &p);
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
-                    bool accumulate, hipStream_t st, std::string *err);
+                    size_t ws_bytes, bool accumulate, hipStream_t st, std::string *err);
 // The single-site problem of site j of an all-sites problem.
 Problem all_site_problem(const AllProblem &p, int64_t j);
 

@@ -8,8 +8,10 @@ import ctypes
 import numpy as np
 import pytest
 
+import oracle
 import paper_2607_09694_amd as lr
 from paper_2607_09694_amd.inputs import FULL, PROJECTED, SLICED, make_host_problem
+from parity import check_dq
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -90,6 +92,22 @@ def test_noalloc_matches_workspace_backward(dev, mode, big, small, dtype):
         assert same_bits(dV0, dV1), "dV"
         assert same_bits(dK0, dK1), "dK"
         assert same_bits(dq0, dq1), "dq"
+
+
+# (S, N, d): bf16 full-rank keys, whose register form keeps 256 bytes a token in
+# the array: few tokens (one range), then more than the array holds, in three
+# ranges of whole rounds over the dq shares (the last one short) and in two.
+FULL_BF16 = [(12, 300, 256), (5, 31, 136), (3, 70001, 64), (2, 33000, 1000), (17, 32001, 72)]
+
+
+@pytest.mark.parametrize("S,N,d", FULL_BF16)
+def test_noalloc_full_rank_bf16_matches_workspace_backward(dev, S, N, d):
+    lib = lr.load_library()
+    (dV0, _, dq0), (dV1, _, dq1) = both_backwards(lib, dev, FULL, S, N, d, d, "bf16", seed=S + N)
+    assert same_bits(dV0, dV1), "dV"
+    assert same_bits(dq0, dq1), "dq"
+    p = make_host_problem(FULL, S, N, d, d, dtype="bf16", seed=S + N, with_dH=True)
+    check_dq("dq", dq1.cpu().numpy(), oracle.route_bwd(p.V, None, p.q, p.dH, FULL, r=d)[2])
 
 
 def test_noalloc_no_tokens_writes_zero_dq(dev):
