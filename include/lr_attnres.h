@@ -488,8 +488,8 @@ int lr_attnres_route_all_fwd(const void *V, const void *K, const float *Q, void 
  * gradient to bf16 once; sliced keys of r > 64 and full-rank keys (any number
  * of tokens; S and T at most 64, d and r multiples of 8, Q 16-byte aligned)
  * take three launches and likewise round each gradient once; with full-rank
- * keys of d < 1024, or d = 1024 and N <= 16384, dQ row j is then bit for bit
- * site j's dq of lr_attnres_route_bwd.
+ * keys of d <= 1024 (with d = 512 or 1024 where N d <= 2^22), dQ row j is then
+ * bit for bit site j's dq of lr_attnres_route_bwd.
  * Otherwise (fp32 storage, larger S or T, wide projected keys, other d or r)
  * the sites run one after the other as accumulating
  * lr_attnres_route_bwd calls over their prefixes, after a fill kernel has

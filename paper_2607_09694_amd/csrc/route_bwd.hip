@@ -261,10 +261,9 @@ int launch_bwd(const Problem &p, const void *dH, void *dV, void *dK, float *dq, 
     // One site of full-rank keys: the all-sites form for one (the same bits in
     // dq).  The rows are read once for the dots and dV and once more for dq, by
     // workgroups per token (step with its forward, 49 sources, d = 1024: 304 ->
-    // 35 us at 64 tokens, 488 -> 353 at 4096, 1443 -> 1388 at 16384).  Wider
-    // rows don't fit its registers; there route_bwd_full is ahead from about
-    // 4000 tokens on (1292 against 1938 us at 50 sources, d = 2048, 8192
-    // tokens).
+    // 35 us at 64 tokens, 488 -> 353 at 4096).  Wider rows don't fit its
+    // registers; there route_bwd_full is ahead from about 4000 tokens on (1292
+    // against 1938 us at 50 sources, d = 2048, 8192 tokens).
     const AllProblem one{p.V, p.K, p.q, nullptr, nullptr, p.S, p.N, p.d, p.r, p.S, 1,
                          p.mode, p.dtype, p.eps};
     if (p.N > 0 && p.S > 1 && full_rows(p) && all_wide(one))
