@@ -26,10 +26,15 @@ constexpr int64_t kWgSplitFull = 1024;
 #endif
 
 // Tokens up to which the low-rank backward splits each token's sources over a
-// workgroup.  Step of forward and backward, one wave per token -> split: 49
-// sources, d = 1024, r = 16: 46 -> 27 us at 128 tokens, 52 -> 39 at 512, 67 ->
-// 68 at 1024; 64 sources, d = 2048: 81 -> 39, 103 -> 91, 146 -> 156.
+// workgroup, from this many sources on: up to 8 are one batch of loads for a
+// wave, so that a quarter of them each wins nothing and the meeting costs.
+// One wave per token / split: 2 to 8 sources of d = 1024, r = 128 0.90 to 1.0 up
+// to 256 tokens, 0.77 to 0.87 at 512; 9 and more at least 0.98 everywhere.  Step
+// of forward and backward, one wave per token -> split: 49 sources, d = 1024, r
+// = 16: 46 -> 27 us at 128 tokens, 52 -> 39 at 512, 67 -> 68 at 1024; 64
+// sources, d = 2048: 81 -> 39, 103 -> 91, 146 -> 156.
 constexpr int64_t kWgSplitBwd = 512;
+constexpr int64_t kWgSplitBwdSources = 9;
 
 // Workgroups below which a backward gives its waves fewer tokens (two per CU).
 constexpr int64_t kFewBlocks = 512;
@@ -111,7 +116,8 @@ bool make_plan(const Problem &p, bool bwd, Plan *pl, std::string *why, bool spli
                (p.N / (kWaves * (pl->tpw / 2)) + 1) * ncols * (int64_t)sizeof(float) <=
                    (int64_t)kNoAllocScratchBytes)
             pl->tpw /= 2;
-        pl->wg_split = split && p.mode != LRAR_MODE_FULL && p.S >= 2 && p.N <= kWgSplitBwd;
+        pl->wg_split = split && p.mode != LRAR_MODE_FULL && p.S >= kWgSplitBwdSources &&
+                       p.N <= kWgSplitBwd;
         const int64_t per_block = pl->wg_split ? 1 : (int64_t)kWaves * pl->tpw;
         if (pl->wg_split)
             pl->tpw = 1;
@@ -141,11 +147,10 @@ int check_supported(const Problem &p, bool bwd, std::string *why)
 
 size_t bwd_partial_bytes(const Problem &p)
 {
-    // Of a site of two sources or more: one source alone may need fewer rows
-    // (plan: its token is not split), but a buffer sized for the first site of
-    // a pass serves them all.
+    // Of a site of many sources: few may need fewer rows (their tokens are not
+    // split), but a buffer sized for the first site of a pass serves them all.
     Problem q = p;
-    q.S = std::max<int64_t>(p.S, 2);
+    q.S = std::max(p.S, kWgSplitBwdSources);
     Plan pl;
     std::string why;
     if (!make_plan(q, true, &pl, &why))

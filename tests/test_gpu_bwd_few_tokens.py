@@ -16,9 +16,9 @@ torch = pytest.importorskip("torch")
 
 # (mode, dtype, S, N, d, r)
 CASES = [
-    (PROJECTED, "bf16", 2, 512, 64, 8),     # two waves without sources
+    (PROJECTED, "bf16", 2, 512, 64, 8),
     (PROJECTED, "bf16", 2, 513, 64, 8),     # the first size past the split
-    (SLICED, "bf16", 5, 512, 200, 24),      # three waves of two sources and fewer
+    (SLICED, "bf16", 5, 512, 200, 24),
     (SLICED, "bf16", 5, 513, 200, 24),
     (PROJECTED, "f32", 37, 511, 100, 12),   # ten sources a wave, the last one seven
     (SLICED, "f32", 6, 1, 1028, 20),        # one token
@@ -26,6 +26,16 @@ CASES = [
     (PROJECTED, "bf16", 3, 2049, 64, 16),   # past one token per wave
     (SLICED, "bf16", 3, 4097, 72, 8),       # past two
     (FULL, "f32", 3, 4097, 40, 40),
+]
+
+# Both sides of the least sources of a split: 9 (waves of 3, 3, 3 and none) and
+# 10 (3, 3, 3, 1) beside 8.
+CASES += [
+    (PROJECTED, "bf16", 8, 512, 64, 8),
+    (PROJECTED, "bf16", 9, 512, 64, 8),
+    (SLICED, "bf16", 10, 512, 200, 24),
+    (PROJECTED, "f32", 9, 511, 100, 12),
+    (SLICED, "f32", 13, 1, 1028, 20),
 ]
 
 
