@@ -487,12 +487,21 @@ void launch_few_tile(const ProjArgs &a, hipStream_t st)
     hipLaunchKernelGGL((key_proj_few<RT, CT>), grid, dim3(kFewThreads), 0, st, a);
 }
 
-// Measured, 256 x 256 tiles -> few-token tiles (d = 1024 unless said): m = 1024:
-// 30 -> 9.6 us at 1 to 128 tokens, 32 -> 24 at 1024; m = 2816: 70 -> 17 at 64,
-// 73 -> 51 at 1024; m = 4096, d = 2048: 100 -> 21 at 64, 103 -> 91 at 1024 (528
-// tiles of 64 x 64); at 2048 tokens (544 tiles) 33 -> 35 and 76 -> 77.  So the
-// line lies at the number of 64 x 64 tiles, about two per CU.
-constexpr int64_t kFewTiles = 528;
+// Tiles of 64 x 64 up to which the few-token form is taken.  256 x 256 tiles ->
+// few-token tiles (1040 outputs unless said): m = 1024: 30 -> 9.6 us at 1 to
+// 128 tokens, 32 -> 13 at 1024 (272 tiles); m = 2816: 71 -> 17 at 64, 73 -> 27 at
+// 1024; 2064 outputs, m = 4096: 103 -> 92 at 1024 (528 tiles), m = 512: 21 -> 22.
+// Short sums make the large tiles cheap: m = 128: 12 -> 9 at 136 tiles, 12 -> 15
+// at 272.  So do narrow outputs, whose one column tile is narrow too: 128
+// outputs, m = 1024: 21 -> 13 at 6000 tokens (188 tiles), 21 -> 23 at 8448 (264);
+// 64 outputs, m = 128: 7 -> 6 at 3000 tokens (47 tiles), 7 -> 9 at 4096 (64).
+int64_t few_tiles_max(const ProjArgs &a)
+{
+    if (a.d + a.r <= kPN)
+        return a.m < 512 ? 63 : 192;
+    return a.m < 512 ? 256 : 512;
+}
+
 // 64 columns a workgroup from this many tiles on (m = 2816, 256 tokens, 68
 // tiles: 31 -> 26 us); 16 below, where more workgroups count for more than
 // reading the tokens' rows less often (64 tokens, 17 tiles).
@@ -605,7 +614,7 @@ int launch_key_proj(const KeyProjProblem &p, hipStream_t st, std::string *err)
     a.ovec = p.d % 8 == 0 && reinterpret_cast<uintptr_t>(p.O) % 16 == 0;
     a.kvec = p.d % 8 == 0 && p.r % 8 == 0 && reinterpret_cast<uintptr_t>(p.K) % 16 == 0;
     a.ncol = key_proj_col_tiles(p.d + p.r);
-    if (few_tiles(a) <= kFewTiles) {
+    if (few_tiles(a) <= few_tiles_max(a)) {
         launch_few(a, st);
         return hip_status(hipGetLastError(), "key_proj_few launch", err);
     }

@@ -24,6 +24,15 @@ CASES = [
     (4097, 40, 520, 24),
 ]
 
+# Both sides of the tiles up to which the few-token form is taken, by width and
+# sum: narrow outputs (63 tiles and 192), wide ones (256 and 512).
+CASES += [
+    (4032, 64, 48, 16), (4033, 64, 48, 16),
+    (12288, 512, 40, 20), (12289, 512, 40, 20),
+    (1024, 72, 1000, 24), (1025, 72, 1000, 24),
+    (2048, 512, 1000, 24), (2049, 512, 1000, 24),
+]
+
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "N{}-m{}-d{}-r{}".format(*c))
 def test_key_projection_tiles_match_oracle(dev, case):  # noqa: F811
