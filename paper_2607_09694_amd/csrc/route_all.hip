@@ -47,7 +47,9 @@ namespace {
 // Full-rank forwards of up to this many tokens run site by site, so that there
 // every row of H stays bit for bit the single-site call's (which splits a
 // token's sources over a workgroup up to the same count, in an order of sums
-// that the wide form doesn't have); with more, one pass over the stack.
+// that the wide form doesn't have); with more, one pass over the stack.  The
+// bits decide, not the time: 49 sources, 48 sites, d = 1024 take 1.58 ms at 64
+// tokens and 2.83 at 1024, one pass 0.022 and 0.083.
 constexpr int64_t kFullSitesOneByOne = 1024;
 
 constexpr int kAllFwdGrid = 256;  // persistent workgroups above 48 sites (one per CU)

@@ -554,12 +554,15 @@ route_fwd_full_1p(const T *__restrict__ V, const float *__restrict__ q, T *__res
 namespace {
 
 // Tokens up to which a wave of route_fwd_lr takes one token: two a wave leave
-// half of the waves of a round (256 CUs, 16 waves each) without work there,
-// and the rest have too few loads in flight.  Two tokens -> one: sliced r =
-// 64, 33 sources, d = 1024: 2100 tokens 50 -> 32 us, 4099 tokens 57 -> 47 us
-// (5.0 -> 6.0 TB/s), 5600 tokens 65 -> 66; projected r = 16, 49 sources: d =
-// 2048, 3000 tokens 134 -> 89, 4096 tokens 144 -> 123; d = 1024, 4608 tokens
-// 79 -> 78, 5120 tokens 81 -> 83; fp32, 33 sources, 4500 tokens 99 -> 100.
+// half of the waves of a round (256 CUs, 16 waves each, 4096 tokens) without
+// work there, and the rest have too few loads in flight.  The gain runs out
+// with that round and is gone a little past it, where the line lies.  Two
+// tokens -> one: sliced r = 64, 33 sources, d = 1024: 2100 tokens 50 -> 32 us,
+// 4099 tokens 57 -> 47 us (5.0 -> 6.0 TB/s), 5600 tokens 65 -> 66; projected r =
+// 16, 49 sources: d = 2048, 3000 tokens 134 -> 89, 4096 tokens 144 -> 123; d =
+// 1024, 4608 tokens 79 -> 78, 5120 tokens 81 -> 83; fp32, 33 sources, 4500
+// tokens 99 -> 100.  4352 tokens, 1 to 64 sources of 64 to 2048 columns: 0.94
+// to 1.5 times as fast (one source 0.95).
 constexpr int64_t kOneTokenFwd = 4352;
 
 template <typename T, int VEC>

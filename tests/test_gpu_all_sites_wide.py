@@ -193,3 +193,105 @@ def test_full_rank_rows_of_one_pass_are_the_single_sites(dev, N, d):  # noqa: F8
         _, _, dq = lr.route_bwd(V[:n_src], None, Qd[j].contiguous(), dHd[j], FULL)
         torch.cuda.synchronize()
         assert torch.equal(dQ[j], dq), f"{n_src} sources"
+
+
+@pytest.mark.parametrize("mode,N,r", [(SLICED, 5, 128), (FULL, 1030, 256)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_non_finite_values_stay_with_their_readers_when_adding(dev, value, mode, N, r):  # noqa: F811
+    """As test_wide_keys_confine_non_finite_values, gradients added to what is
+    there, and with full-rank keys, where a non-finite value is a key too."""
+    S, T, first, d, n, column = 14, 12, 2, 256, 2, 40
+    _, _, _, V, Qd, dHd = _run(dev, (S, T, first, N, d, r), seed=19)
+    base = torch.randn((S, N, d), device=dev).to(torch.bfloat16)
+
+    def add(V, dH):
+        out = (base.clone(), None, torch.ones_like(Qd))
+        lr.route_all_bwd(V, None, Qd, dH, mode, first, out=out, accumulate=True)
+        return out[0], out[2]
+
+    dV0, dQ0 = add(V, dHd)
+    # an upstream value of the first site: sources that this site reads
+    dHb = dHd.clone()
+    dHb[0, n, column] = value
+    dV, dQ = add(V, dHb)
+    torch.cuda.synchronize()
+    tokens = [t for t in range(N) if t != n]
+    assert torch.equal(dV[:, tokens], dV0[:, tokens])
+    assert torch.allclose(dV[first:].float(), dV0[first:].float(), rtol=2.0 ** -7, atol=1e-3)
+    assert not bool(torch.isfinite(dV[:first, n, column].float()).any())
+    assert torch.allclose(dQ[1:], dQ0[1:], rtol=1e-4, atol=1e-3)
+    # a source value: the sites that read it, and through them all they read
+    Vb = V.clone()
+    Vb[11, n, column] = value
+    H0, _ = lr.route_all_fwd(V, None, Qd, mode, first)
+    H, _ = lr.route_all_fwd(Vb, None, Qd, mode, first)
+    dV, dQ = add(Vb, dHd)
+    torch.cuda.synchronize()
+    readers = [j for j in range(T) if first + j > 11]
+    others = [j for j in range(T) if first + j <= 11]
+    assert torch.equal(H[:, tokens], H0[:, tokens])
+    assert torch.allclose(H[others].float(), H0[others].float(), rtol=2.0 ** -7, atol=1e-6)
+    assert not bool(torch.isfinite(H[readers][:, n, column].float()).any())
+    assert torch.equal(dV[:, tokens], dV0[:, tokens])
+    assert torch.allclose(dQ[others], dQ0[others], rtol=1e-4, atol=1e-3)
+    assert not bool(torch.isfinite(dQ[readers]).any())
+    assert torch.equal(dV[13, n], dV0[13, n])  # read by no site
+
+
+def _dq64(V, q, dH, r, eps=1e-6):
+    """dq [r] of one site in fp64 by torch, in chunks of tokens."""
+    out = torch.zeros((r,), dtype=torch.float64, device=V.device)
+    for b in range(0, V.shape[1], 2000):
+        x = V[:, b:b + 2000].double()
+        k = x[..., x.shape[2] - r:]
+        kb = k / (k.square().mean(-1, keepdim=True) + eps).sqrt()
+        a = torch.softmax((kb * q.double()).sum(-1), dim=0)
+        g = (x * dH[b:b + 2000].double()).sum(-1)
+        ds = a * (g - (a * g).sum(0))
+        out += (ds[..., None] * kb).sum((0, 1))
+    return out.cpu().numpy()
+
+
+def test_stack_beyond_2_31_elements(dev):  # noqa: F811
+    """64-bit plane offsets in the one pass over the stack and in the register
+    form of one full-rank site: sampled tokens against the oracle, the last
+    ones among them, and rows of dQ over all tokens."""
+    S, T, first, N, d, r = 33, 32, 2, 66000, 1000, 72
+    assert S * N * d > 2 ** 31
+    g = torch.Generator(device=dev)
+    g.manual_seed(7)
+    V = torch.empty((S, N, d), dtype=torch.bfloat16, device=dev)
+    dH = torch.empty((T, N, d), dtype=torch.bfloat16, device=dev)
+    for i in range(S):
+        V[i].copy_(torch.randn((N, d), generator=g, device=dev))
+    for j in range(T):
+        dH[j].copy_(torch.randn((N, d), generator=g, device=dev))
+    Q = torch.randn((T, r), generator=g, device=dev) * (2.0 / r ** 0.5)
+    H, ne = lr.route_all_fwd(V, None, Q, SLICED, first)
+    dV, _, dQ = lr.route_all_bwd(V, None, Q, dH, SLICED, first)
+    torch.cuda.synchronize()
+    toks = torch.as_tensor([0, 1, 32768, N // 2 + 1, N - 2, N - 1], device=dev)
+
+    def host(x):
+        return x[:, toks].contiguous()
+
+    def bits(x):
+        return host(x).view(torch.int16).cpu().numpy().view(np.uint16)
+
+    Qh = Q.cpu().numpy().astype(np.float64)
+    rH, rne = oracle.route_all_fwd(bits(V), None, Qh, SLICED, first, r=r)
+    rV, _, _ = oracle.route_all_bwd(bits(V), None, Qh, bits(dH), SLICED, first, r=r)
+    check_bf16_grown("H", to_host(host(H)), rH)
+    check_f32("neff", to_host(host(ne)), rne)
+    check_bf16_grown("dV", to_host(host(dV))[..., :d - r], rV[..., :d - r])
+    check_bf16_key_grad("dV key columns", to_host(host(dV))[..., d - r:], rV[..., d - r:])
+    for j in (0, T - 1):
+        check_dq(f"dQ row {j}", to_host(dQ[j]), _dq64(V[:first + j], Q[j], dH[j], r))
+    del H, ne
+    q = torch.randn((d,), generator=g, device=dev) * (2.0 / d ** 0.5)
+    _, _, dq = lr.route_bwd(V, None, q, dH[0], FULL, out=(dV, None, torch.empty_like(q)))
+    torch.cuda.synchronize()
+    oV, _, _ = oracle.route_bwd(bits(V), None, q.cpu().numpy().astype(np.float64), bits(dH)[0], FULL,
+                                r=d)
+    check_bf16_grown("single-site dV", to_host(host(dV)), oV)
+    check_dq("single-site dq", to_host(dq), _dq64(V, q, dH[0], d))
