@@ -51,7 +51,7 @@ def bwd_bytes(S, N, d, r):
 
 # The sources that define the measured backward and forward kernels; the
 # committed counter summary is valid only while these are unchanged.
-KERNEL_FILES = ("route_bwd.hip", "route_fwd.hip", "route_common.h", "route_device.h")
+KERNEL_FILES = ("route_bwd.hip", "route_bwd_lr.h", "route_fwd.hip", "route_common.h", "route_device.h")
 
 
 def kernel_source_hash():
