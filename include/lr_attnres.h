@@ -147,11 +147,11 @@ int lr_attnres_route_bwd_accumulate(const void *V, const void *K, const float *q
  * that device's first call).  The call itself allocates nothing, on the
  * device or through any library routine.
  *   Arguments, results, validation and errors are those of
- *   lr_attnres_route_bwd with the workspace removed, plus LRAR_EUNSUPPORTED
- *   when the problem needs more than 8 MiB of partials
- *   (the form that uses a larger workspace is not taken then; e.g. r = 32 beyond
- *   2^19 tokens with projected keys, or full rank at d = 1024 beyond
- *   32768 tokens).
+ *   lr_attnres_route_bwd with the workspace removed, bit for bit, plus
+ *   LRAR_EUNSUPPORTED when the problem needs more than 8 MiB of dq partials
+ *   (e.g. r = 32 beyond 2^19 tokens with projected keys, or full rank at
+ *   d = 1024 beyond 32768 tokens).  What the full-rank form of bf16 storage
+ *   keeps per token goes through the array in ranges of tokens.
  *   All calls on one device share the array, and each call leaves its
  *   partials there: two calls that can run at the same time on one device
  *   (different streams, or different host threads without ordering) race
@@ -452,9 +452,11 @@ int lr_attnres_route_gather_bwd(const void *V, const void *K, int64_t source, co
  * 8, one fused launch reads the stack once for all sites; so does a second
  * form for sliced keys of any r > 64 and, above 1024 tokens, full-rank keys
  * (bf16 storage, S and T at most 64, d and r multiples of 8, Q 16-byte
- * aligned).  Otherwise (full-rank keys of up to 1024 tokens, larger S or T,
- * wide projected keys, wide keys in fp32, other d or r) the library runs the
- * sites one after the other, each as lr_attnres_route_fwd over its prefix (and
+ * aligned, fewer than 2^24 tokens), where it is ahead of the sites: the more
+ * tokens, the more sites and rows these must read.  Otherwise (few such sites,
+ * full-rank keys of up to 1024 tokens, larger S or T, wide projected keys, wide
+ * keys in fp32, other d or r) the library runs the sites one after the other,
+ * each as lr_attnres_route_fwd over its prefix (and
  * lr_attnres_route_neff), so every site's H row is bit for bit that call's.
  * EINVAL: first < 1, T < 1, first + T - 1 > S, or the conditions of
  * lr_attnres_route_fwd (V, H 16-byte aligned; K, Q, neff element aligned; no
@@ -485,12 +487,14 @@ int lr_attnres_route_all_fwd(const void *V, const void *K, const float *Q, void 
  * accumulate = 0 overwrites dV, dK and dQ; 1 adds the gradients to them.
  * Where the fused forward applies and storage is bf16, one fused launch moves
  * each source row, upstream row and dV row once for all sites and rounds each
- * gradient to bf16 once; sliced keys of r > 64 and full-rank keys (any number
- * of tokens; S and T at most 64, d and r multiples of 8, Q 16-byte aligned)
- * take three launches and likewise round each gradient once; with full-rank
+ * gradient to bf16 once; sliced keys of r > 64 and full-rank keys (S and T at
+ * most 64, d and r multiples of 8, Q 16-byte aligned, fewer than 2^24 tokens)
+ * of three sites and more take three launches, where these are ahead of the
+ * sites, and likewise round each gradient once; with full-rank
  * keys of d <= 1024 (with d = 512 or 1024 where N d <= 2^22), dQ row j is then
  * bit for bit site j's dq of lr_attnres_route_bwd.
- * Otherwise (fp32 storage, larger S or T, wide projected keys, other d or r)
+ * Otherwise (few such sites, fp32 storage, larger S or T, wide projected keys,
+ * other d or r)
  * the sites run one after the other as accumulating
  * lr_attnres_route_bwd calls over their prefixes, after a fill kernel has
  * zeroed dV, dK and dQ when overwriting (no memset); a source's gradient is

@@ -555,10 +555,10 @@ int check_key_proj_supported(const KeyProjProblem &p, std::string *why)
 // 256-wide tiles read half the LDS bytes per product of the backward's 128 x
 // 128 ones, which are bound by those reads.  One such workgroup fills a CU, so
 // the rule asks for one tile per CU and for rounds of 256 tiles that are
-// filled to 7/10.  Forward and backward at 1024 + 16 outputs, m = 2816, before
-// -> after: 704 tiles (16384 tokens) 398 -> 367 us, 506 tiles 304 -> 280, 374
-// tiles (filled to 0.73) 248 -> 246; outside it 297 tiles (0.58) 222 -> 228;
-// m = 1024, 128 tiles 101 -> 109.
+// filled to 7/10.  Forward and backward at 1024 + 16 outputs, m = 2816, the
+// best of runs back to back, before -> after: 704 tiles (16384 tokens) 398 ->
+// 367 us, 506 tiles 304 -> 280, 374 tiles (filled to 0.73) 248 -> 246; outside
+// it 297 tiles (0.58) 222 -> 228; m = 1024, 128 tiles 101 -> 109.
 size_t key_proj_da_bytes(const KeyProjProblem &p)
 {
     const int64_t tiles = (int64_t)key_proj_col_tiles(p.m) * ((p.N + kPM - 1) / kPM);

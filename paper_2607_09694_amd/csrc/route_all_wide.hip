@@ -20,21 +20,21 @@
 //        ck_i = sum_j ds s / (rho_i^2 r).
 //   wide_dq (one 64-column slab of the keys and one share of the tokens per
 //     wave): dQ += cq K over its tokens in registers, on the fp32 matrix
-//     cores, then a fixed-order sum of the shares.
+//     cores, then a fixed-order sum of the shares in fp64.
 //
 // The single-site backward of full-rank keys is the same for one site, with
 // its rows in registers (route_bwd_full_rows) and its dQ on the vector units
 // (wide_dq_one): the same operations in the same order for every element of D,
 // G, the softmax, cq and dQ, whichever sites are computed beside it, so that
-// row j of an all-sites dQ is bit for bit the single-site dq of site j (up to
-// the 1024 columns that this form takes).
+// row j of an all-sites dQ is bit for bit the single-site dq of site j where
+// that takes this form (full_rows).
 //
 // Measured at 49 sources, d = 1024.  48 sites, 2048 tokens: sliced r = 256, 48
-// x (77 + dq 5) us site by site before; now 255 + 44 + 6 us (0.61 GB of rows
-// in and out at least).  Full rank: 48 x (212 + dq 5) us before; now 314 + 130
+// x (77 + dq 5) us site by site before; now 265 + 44 + 6 us (0.61 GB of rows
+// in and out at least).  Full rank: 48 x (212 + dq 5) us before; now 335 + 131
 // + 5 us: the fp32 matrix cores bound wide_dq, rows read again in part 2 and
 // its short phases the rest.  One full-rank site, 4096 tokens: 447 + 5 us
-// before (two reads of the rows at 256 workgroups); now 204 + 94 + 5 us (0.82
+// before (two reads of the rows at 256 workgroups); now 220 + 86 + 5 us (0.82
 // GB in and out, then 0.41 GB again for dq).
 #include "route_all_weights.h"
 
