@@ -491,16 +491,17 @@ int lr_attnres_route_all_fwd(const void *V, const void *K, const float *Q, void 
  * most 64, d and r multiples of 8, Q 16-byte aligned, fewer than 2^24 tokens)
  * of three sites and more take three launches, where these are ahead of the
  * sites, and likewise round each gradient once; with full-rank
- * keys of d <= 1024 (with d = 512 or 1024 where N d <= 2^22), dQ row j is then
- * bit for bit site j's dq of lr_attnres_route_bwd.
+ * keys of d < 1024, or d = 1024 and N <= 16384, dQ row j is then bit for bit
+ * site j's dq of lr_attnres_route_bwd.
  * Otherwise (few such sites, fp32 storage, larger S or T, wide projected keys,
  * other d or r)
  * the sites run one after the other as accumulating
  * lr_attnres_route_bwd calls over their prefixes, after a fill kernel has
  * zeroed dV, dK and dQ when overwriting (no memset); a source's gradient is
  * then rounded to the storage after each site that reads it, and dQ row j is
- * bit for bit site j's dq.  Either way dQ is reduced in a fixed order, so
- * results are bitwise reproducible.
+ * bit for bit site j's dq of that accumulating call.  (One site that reads the
+ * whole stack is one lr_attnres_route_bwd call when overwriting.)  Either way dQ
+ * is reduced in a fixed order, so results are bitwise reproducible.
  * EINVAL as for lr_attnres_route_all_fwd, plus dH, dV 16-byte aligned, dK and
  * dQ element aligned, a too small workspace, accumulate not 0 or 1, and any
  * output (or the workspace) overlapping an input or another output.

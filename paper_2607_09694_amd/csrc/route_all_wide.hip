@@ -1020,21 +1020,28 @@ void launch_full_rows(const WideBwdArgs &b, hipStream_t st)
 
 }  // namespace
 
-// Rows of 512 or 1024 columns, which route_bwd_full takes without column
-// masks, leave the register form behind above 2^22 tokens x columns
-// (route_bwd_full / this, 2, 4, 16, 49 sources; adding to the gradients in
-// brackets): d = 1024: 4096 tokens 1.12, 1.17, 1.45, 1.48 (0.96, 1.00, 1.42,
-// 1.16), 8192: 0.85, 0.90, 1.05, 1.02 (0.79, 0.88, 0.86, 0.86); d = 512: 8192
-// 1.20, 1.16, 1.37, 1.53 (1.09, 1.05, 1.28, 1.11), 16384: 1.02, 0.87, 1.10, 1.14
-// (0.86, 0.81, 0.88, 0.96).  Rows of 1000 columns gain throughout but around
-// 12000 tokens, where route_bwd_full's workgroups fill the chip exactly: 16384
-// 1.10, 1.26, 1.37 (0.95, 1.18, 1.09).  The same line for both, so that adding to
-// zeros gives the same bits.
+// Rows of 1024 columns, which route_bwd_full takes without column masks, leave
+// the register form level with it at 32 sources and behind with fewer from
+// about 16384 tokens on (route_bwd_full -> this: 16001 tokens, 4 sources 103 ->
+// 101 us, 16: 357 -> 317; 24000 tokens, 2: 84 -> 107, 16: 411 -> 460, 32: 898 ->
+// 898; 60001 tokens, 16: 986 -> 1115).  Rows of 1000 columns gain throughout
+// (60001 tokens, 2: 285 -> 283, 16: 1463 -> 1251).  Up to that line the form is
+// kept for few sources too, where it costs up to 15% (8192 tokens, 2 sources),
+// for the bits that it shares with the all-sites form.
 bool full_rows(const Problem &p)
 {
     return p.mode == LRAR_MODE_FULL && p.dtype == LRAR_DTYPE_BF16 && p.d % 8 == 0 &&
-           p.d <= kFullRowsMax && (p.d % 512 != 0 || p.N <= (1 << 22) / p.d) &&
+           p.d <= kFullRowsMax && (p.d < kFullRowsMax || p.N <= 16384) &&
            p.N * kBlock < ((int64_t)1 << 32);
+}
+
+// Adding to the gradients, also rows of 512 columns fall behind, and from 2^22
+// tokens x columns on (route_bwd_full / this, 2, 4, 16, 49 sources): d = 1024:
+// 4096 tokens 0.96, 1.00, 1.42, 1.16, 8192: 0.79, 0.88, 0.86, 0.86; d = 512: 8192
+// 1.09, 1.05, 1.28, 1.11, 16384: 0.86, 0.81, 0.88, 0.96.
+bool full_rows_adding(const Problem &p)
+{
+    return full_rows(p) && (p.d % 512 != 0 || p.N <= (1 << 22) / p.d);
 }
 
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,

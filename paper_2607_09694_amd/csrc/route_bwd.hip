@@ -266,7 +266,7 @@ int launch_bwd(const Problem &p, const void *dH, void *dV, void *dK, float *dq, 
     // against 1938 us at 50 sources, d = 2048, 8192 tokens).
     const AllProblem one{p.V, p.K, p.q, nullptr, nullptr, p.S, p.N, p.d, p.r, p.S, 1,
                          p.mode, p.dtype, p.eps};
-    if (p.N > 0 && p.S > 1 && full_rows(p) && all_wide(one))
+    if (p.N > 0 && p.S > 1 && (accumulate ? full_rows_adding(p) : full_rows(p)) && all_wide(one))
         return launch_wide_bwd(one, dH, dV, dq, ws, ws_bytes, accumulate, st, err);
     float *partial = static_cast<float *>(ws);
     const hipError_t e =

@@ -182,6 +182,7 @@ size_t wide_bwd_workspace_bytes(int64_t N, int64_t T, int64_t r);
 // whether storage, keys and rows suit that form (2 to 64 sources take it).
 constexpr int64_t kFullRowsMax = 1024;
 bool full_rows(const Problem &p);
+bool full_rows_adding(const Problem &p);  // where it adds to the gradients
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
                     size_t ws_bytes, bool accumulate, hipStream_t st, std::string *err);
 // The single-site problem of site j of an all-sites problem.

@@ -73,7 +73,7 @@ def _single(S, N, d, r, mode, dtype):
 
 
 @pytest.mark.parametrize("S,N,d,shares", [
-    (49, 16384, 1000, 64), (2, 16384, 1000, 64), (64, 100000, 64, 1024), (100, 1000, 512, 128),
+    (49, 16384, 1024, 64), (2, 16384, 1000, 64), (64, 100000, 64, 1024), (100, 1000, 512, 128),
 ])
 def test_one_full_rank_site_asks_for_one_site(S, N, d, shares):
     """The softmax gradients of each token at one site and the dq shares, or
@@ -82,7 +82,7 @@ def test_one_full_rank_site_asks_for_one_site(S, N, d, shares):
     assert rows <= _single(S, N, d, d, lr.FULL, BF16) <= max(rows, -(-N // 4) * d * 4)
 
 
-@pytest.mark.parametrize("S,N,d,dtype", [(64, 16384, 2048, BF16), (49, 16384, 1020, BF16), (49, 8193, 512, BF16), (49, 16384, 1024, BF16),
+@pytest.mark.parametrize("S,N,d,dtype", [(64, 16384, 2048, BF16), (49, 16384, 1020, BF16), (49, 16385, 1024, BF16),
                                          (49, 16384, 1024, F32), (49, 1 << 24, 64, BF16)])
 def test_full_rank_sites_of_other_forms_ask_for_dq_partials(S, N, d, dtype):
     assert _single(S, N, d, d, lr.FULL, dtype) == -(-N // 16) * d * 4
