@@ -37,7 +37,13 @@ constexpr int64_t kWgSplitBwd = 512;
 constexpr int64_t kWgSplitBwdSources = 9;
 
 // Workgroups below which a backward gives its waves fewer tokens (two per CU).
+// Full-rank rows, read twice by a wave with many loads of its own, gain from it
+// only below one per CU (rows above 2 KiB) or one and a half: four tokens a
+// wave / two, 2 and 24 sources: bf16, d = 1280: 5000 tokens 0.94, 1.01, 7000
+// 0.87, 1.00; d = 2048: 5000 0.91, 0.92; fp32, d = 512: 5000 1.34, 1.39; bf16, d =
+// 1024: 6000 1.25, 1.21, 7000 0.94, 0.87.
 constexpr int64_t kFewBlocks = 512;
+constexpr int64_t kFewBlocksFull = 384, kFewBlocksWide = 256;
 
 int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
@@ -112,7 +118,11 @@ bool make_plan(const Problem &p, bool bwd, Plan *pl, std::string *why, bool spli
         // 127; at twice kFewBlocks level or 1% slower).  The dq partials, one
         // row a workgroup, stay within what a caller without a workspace has.
         const int64_t ncols = p.mode == LRAR_MODE_FULL ? p.d : p.r;
-        while (pl->tpw > 1 && p.N < kFewBlocks * kWaves * pl->tpw &&
+        const int64_t few = p.mode != LRAR_MODE_FULL ? kFewBlocks
+                            : p.d * (p.dtype == LRAR_DTYPE_BF16 ? 2 : 4) > 2048 ? kFewBlocksWide
+                                                                                : kFewBlocksFull;
+        const bool fewer = p.N < few * kWaves * pl->tpw;
+        while (fewer && pl->tpw > 1 && p.N < kFewBlocks * kWaves * pl->tpw &&
                (p.N / (kWaves * (pl->tpw / 2)) + 1) * ncols * (int64_t)sizeof(float) <=
                    (int64_t)kNoAllocScratchBytes)
             pl->tpw /= 2;
