@@ -1035,13 +1035,16 @@ bool full_rows(const Problem &p)
            p.N * kBlock < ((int64_t)1 << 32);
 }
 
-// Adding to the gradients, also rows of 512 columns fall behind, and from 2^22
-// tokens x columns on (route_bwd_full / this, 2, 4, 16, 49 sources): d = 1024:
-// 4096 tokens 0.96, 1.00, 1.42, 1.16, 8192: 0.79, 0.88, 0.86, 0.86; d = 512: 8192
-// 1.09, 1.05, 1.28, 1.11, 16384: 0.86, 0.81, 0.88, 0.96.
+// Adding to the gradients, rows of 512 columns fall behind too, and all wide
+// ones earlier (route_bwd_full / this, 2, 4, 16, 32 or 49 sources): d = 1024: 4096
+// tokens 0.96, 1.00, 1.42, 1.16, 8192: 0.79, 0.88, 0.86, 0.86; d = 512: 8192 1.09,
+// 1.05, 1.28, 1.11, 16384: 0.86, 0.81, 0.88, 0.96; d = 1000: 6000 0.99, 1.07, 1.37,
+// 1.28, 12288: 0.72, 0.84, 0.86, 0.88, 24000: 0.76, 0.83, 0.88; d = 776: 8000 0.92,
+// 1.02, 1.17, 1.14, 24000 0.76, 0.96, 0.88, 0.88.
 bool full_rows_adding(const Problem &p)
 {
-    return full_rows(p) && (p.d % 512 != 0 || p.N <= (1 << 22) / p.d);
+    const int64_t most = p.d % 512 == 0 ? 1 << 22 : 6 << 20;  // tokens x columns
+    return full_rows(p) && (p.d < 512 || p.N * p.d <= most);
 }
 
 int launch_wide_bwd(const AllProblem &p, const void *dH, void *dV, float *dQ, void *ws,
